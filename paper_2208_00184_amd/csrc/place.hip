@@ -7,14 +7,12 @@
 // (source cluster, edge id) and runs of equal source cluster summed, which
 // gives each cluster its list of coarse in-edges (pred, comm) in a fixed order.
 //
-// Placement (sequential over clusters, as the algorithm is): one wave.  For
-// cluster t, pre_t on device x is max over preds of Fin[p] + I(dev p != x)
-// cc; it is evaluated for all devices at once from the largest Fin + cc over
-// the preds, one device reaching it, and two more maxima (wave reductions
-// over the preds, one per lane).  Lane x then finds the first-fit start on
-// device x in that device's sorted list of busy blocks (touching intervals
-// are merged, so the list holds one block per idle gap), and a wave
-// reduction picks the device.
+// Placement (sequential over clusters, as the algorithm is): up to 64 devices
+// by k_place_ahead (one deciding wave, 15 reading ahead), more by k_place (one
+// wave).  Pre_t on device x is max over preds of Fin[p] + I(dev p != x) cc;
+// lane x (mod 64) then finds the first-fit start on device x in that device's
+// sorted list of busy blocks (touching intervals are merged, so the list
+// holds one block per idle gap), and the wave picks the device.
 #include <type_traits>
 
 #include "cel_internal.h"
@@ -252,8 +250,8 @@ constexpr int64_t kPlaceFull = int64_t(1) << 62;  // EST of a device without roo
 constexpr int kPlaceQ = 4;                        // preds per lane held in registers
 constexpr int kPlacePad = 64 * kPlaceQ;           // entries read past the end of a pred list
 
-// Placement, one wave (its LDS accesses are in program order, so no barrier
-// is needed).  For cluster t, pre_t on device x is the largest of 0, Fin[p]
+// Placement on more than 64 devices, one wave (its LDS accesses are in program
+// order, so no barrier is needed).  For cluster t, pre_t on device x is the largest of 0, Fin[p]
 // over preds p on x and Fin[p] + cc over preds on other devices.  With m1 the
 // largest Fin + cc over all preds and d1 the device of one pred reaching it,
 // every device other than d1 has pre_t = m1 (a pred's Fin never exceeds its
@@ -631,11 +629,13 @@ __device__ inline int64_t dur_tm(int64_t w, int64_t tm) {  // ceil(w * tm / 1024
   return (w >> 10) * tm + (((w & 1023) * tm + 1023) >> 10);
 }
 
-// Per node: the cluster's duration on every device (atomics into W2[t][x]),
+// Per node: the cluster's duration at each of the U distinct device speeds
+// (atomics into W2[t][u]; one sum per device took 16 atomics a node on 16
+// devices of two speeds, 0.85 ms at 1.07M nodes),
 // its own memory (followers excluded) and follower counts per cluster.
-__global__ void k_pe_nodes(int32_t n, int32_t C, int32_t D, const int32_t *cid, const int64_t *w,
+__global__ void k_pe_nodes(int32_t n, int32_t C, int32_t U, const int32_t *cid, const int64_t *w,
                            const int64_t *mem, const int32_t *group, const int32_t *lead,
-                           const int64_t *tmul, uint64_t *W2, uint64_t *MEMo, int32_t *fcnt,
+                           const int64_t *umul, uint64_t *W2, uint64_t *MEMo, int32_t *fcnt,
                            Status *st) {
   if (failed(st)) return;
   uint32_t bad = 0;
@@ -647,9 +647,9 @@ __global__ void k_pe_nodes(int32_t n, int32_t C, int32_t D, const int32_t *cid, 
       continue;
     }
     const int64_t wv = w[v];
-    for (int32_t x = 0; x < D; x++)
-      atomicAdd((unsigned long long *)&W2[(int64_t)c * D + x],
-                (unsigned long long)(tmul ? dur_tm(wv, tmul[x]) : wv));
+    for (int32_t u = 0; u < U; u++)
+      atomicAdd((unsigned long long *)&W2[(int64_t)c * U + u],
+                (unsigned long long)dur_tm(wv, umul[u]));
     const int32_t gv = group ? group[v] : -1;
     if (gv >= 0 && lead[gv] < c) atomicAdd(&fcnt[c], 1);
     else atomicAdd((unsigned long long *)&MEMo[c], (unsigned long long)mem[v]);
@@ -705,174 +705,435 @@ __global__ void k_pe_succ(int32_t C, const int32_t *boff, const int32_t *ncp, co
   }
 }
 
-struct PeArgs {
-  int32_t C, D;
-  bool links;                      // per-link tables given
-  const int64_t *cap;              // [D]
-  const uint64_t *W2, *MEMo;       // [C][D] durations, [C] own memory
-  const int32_t *boff, *ncp, *ca;  // coarse in-edges (bucket start, count, source)
-  const int64_t *cc, *cob, *cnum;  // their summed c, ob and member count
-  const uint64_t *back;            // max summed c over out-edges (no link tables)
-  const int32_t *soff;             // [C + 1] out-edges (link tables): OB, N
-  const int64_t *sob, *snum;
-  const int32_t *foff, *fl;        // [C + 1] followers: leading cluster, memory
-  const int64_t *fm;
-  const int64_t *lbw, *llat;       // [D][D] link tables
-  uint8_t *cdev;
-  int64_t *Fin, *bs, *bf;          // busy lists [D][bcap]
-  int32_t bcap;
-};
-
-constexpr int kPeLds = 8192;  // clusters whose Fin and device stay in LDS too
-
 __device__ inline int64_t link_cost(int64_t ob, int64_t cnt, int32_t bw, int32_t lat) {
   return (int64_t)(((uint64_t)ob + (uint64_t)bw - 1) / (uint64_t)bw) + cnt * lat;
 }
 
-// One wave; device x's free memory, busy-list size and last end sit in lane
-// x (D <= 64), its busy blocks in its global list, which only lane x reads
-// and writes.
-template <bool LDSF>
-__global__ void __launch_bounds__(64) k_place_ext(PeArgs a, Status *st) {
-  __shared__ int32_t s_bw[64 * 64], s_lat[64 * 64];
-  __shared__ int64_t s_fin[LDSF ? kPeLds : 1];
-  __shared__ uint8_t s_cd[LDSF ? kPeLds : 1];
-  if (failed(st)) return;
-  const int lane = threadIdx.x;
+// The same with inv = 1.0 / bw at hand.  Below 2^51 the numerator is exact
+// as a double and the product with inv is off by less than one, so one step
+// of correction gives the integer quotient (about ten instructions instead of
+// a 64-bit division).
+__device__ inline int64_t link_cost_inv(int64_t ob, int64_t cnt, int32_t bw, int32_t lat,
+                                        double inv) {
+  const int64_t num = ob + bw - 1;
+  if ((uint64_t)num >> 51) return link_cost(ob, cnt, bw, lat);
+  int64_t q = (int64_t)((double)num * inv);
+  const int64_t r = num - q * bw;
+  q += r < 0 ? -1 : (r >= bw ? 1 : 0);
+  return q + cnt * lat;
+}
+
+// Placement of the clusters in index order for D <= 64, one workgroup: wave 0
+// decides, the other 15 waves read ahead.
+//
+// The clusters come in batches of kPlB = 15.  While wave 0 places batch k,
+// helper wave j + 1 prepares cluster j of batch k + 1: it reads the cluster's
+// sizes and coarse in-edges from global memory and folds the far ones (from
+// clusters before batch k, whose finish times are final) into pre_t of every
+// device, lane x (and its copies x + DP, x + 2 DP, ...) taking device x: that
+// is Fin + I(dev != x) cc, or with link tables the cost on the link dev -> x.
+// The near in-edges (from batch k, or batch k + 1 itself) go to a short list
+// in LDS; the lists are sorted by source, so they are a list's tail, at most
+// 29 entries.  One barrier per batch swaps the two sets of buffers.  Wave 0's
+// step then reads only LDS: the folded pre_t of its lane's device, and for
+// each near in-edge the source's finish time and device, with no reduction
+// over the in-edges at all.
+//
+// Device x's state sits in the registers of wave 0's lanes x, x + DP, ... (DP
+// = 16, 32 or 64 >= D: 64 / DP copies, so that as many near in-edges are read
+// at once, one per copy, and combined by lane swaps): free memory, and of its
+// busy list (merged intervals, one block per idle gap) the size, the end of
+// the last block, its start and the end of the block before.  A cluster ready
+// at or after that end (all but 1 of 6,223 steps on the 1.07M-node transformer
+// graph, 11 of 1,000 on the layered 200k one) finds its start from the
+// registers; an earlier one searches the list.  The cluster stays on the
+// previous one's device unless a device starts it more than back_cost earlier
+// (eq. 9): one compare and ballot; only then is the smallest start found.  A
+// start that extends the last block (97 % of the steps) changes registers
+// only: the last block's end is kept there and written to the list when it is
+// read or when another block follows it.  Lists live in LDS (kBlk / D blocks
+// each) and move to global memory when they outgrow it.
+//
+// What bounds it: the chain of dependent operations of wave 0's step, one
+// wave issuing in order.  1.07M-node transformer graph, 6,223 clusters on 16
+// devices: one wave doing everything, with three wave reductions over the
+// in-edges and waits for their loads, took 6.8 ms (1.09 us a step); this
+// kernel 2.7 ms (0.43 us).  Extended form with link tables: 47 ms (one in-edge
+// at a time, a 64-bit division each) against 5.7 ms.
+constexpr int kPlB = 15;     // clusters per batch, one helper wave each
+constexpr int kPlNear = 32;  // near in-edges of a cluster: at most 2 kPlB - 1, padded to fours
+constexpr int kPlRing = 64;  // finish times and devices of the last batches, by cluster & 63
+
+struct PlaceArgs {
+  int32_t C, D;
+  bool links;                      // EXT: per-link tables given
+  const int64_t *cap;              // [D]
+  const uint64_t *W, *MEM;         // [C] (EXT: W[C][U], one sum per distinct speed)
+  const int32_t *boff, *ncp, *ca;  // coarse in-edges (bucket start, count, source ascending)
+  const int64_t *cc, *cob, *cnum;  // their summed c, ob and member count
+  const uint64_t *back;            // max summed c over out-edges (no link tables)
+  const int32_t *soff;             // [C + 1] out-edges (link tables): OB, N
+  const int64_t *sob, *snum;
+  const int32_t *foff, *fl;        // [C + 1] followers: leading cluster, memory (or NULL)
+  const int64_t *fm;
+  const int64_t *lbw, *llat;       // [D][D] link tables
+  const int32_t *uidx;             // EXT: [D] each device's speed, an index below U
+  int32_t U;
+  uint8_t *cdev;
+  int64_t *Fin, *bs, *bf;          // finish times; busy lists [D][bcap] past their LDS share
+  int32_t bcap;
+};
+
+struct __align__(16) PlFin {   // a placed cluster
+  int64_t fin;
+  int64_t dev;
+};
+struct __align__(16) PlNear {  // a near in-edge: cc (or ob), ring slot << 32 | member count
+  int64_t c;
+  int64_t sn;
+};
+
+// the larger of every lane's value and its copies' (lanes x, x + DP, ...)
+template <int DP>
+__device__ inline int64_t copies_max(int64_t v) {
+  if (DP <= 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+    v = max_nonneg((int64_t)(((uint64_t)hi[0] << 32) | lo[0]), (int64_t)(((uint64_t)hi[1] << 32) | lo[1]));
+  }
+  if (DP <= 16) {
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+    v = max_nonneg((int64_t)(((uint64_t)hi[0] << 32) | lo[0]), (int64_t)(((uint64_t)hi[1] << 32) | lo[1]));
+  }
+  return v;
+}
+
+template <bool EXT, int DP>
+__global__ void __launch_bounds__(64 * (kPlB + 1)) k_place_ahead(PlaceArgs a, Status *st) {
+  constexpr int kBlk = EXT ? 1024 : 3072;
+  __shared__ int64_t s_bs[kBlk], s_bf[kBlk];
+  __shared__ PlFin s_ring[kPlRing + 1];  // the last entry: finish 0, for the lists' padding
+  __shared__ PlNear s_near[2][kPlB][kPlNear];
+  __shared__ int64_t s_pre[2][kPlB][64];
+  __shared__ int64_t s_hdr[2][kPlB][4];  // W, MEM, back, near count
+  __shared__ int64_t s_wx[EXT ? 2 : 1][EXT ? kPlB : 1][64];   // duration by device
+  __shared__ int64_t s_fol[EXT ? 2 : 1][EXT ? kPlB : 1][64];  // follower memory by device
+  __shared__ int64_t s_folw[EXT ? 2 : 1][EXT ? kPlB : 1][kPlNear];  // ... by near leading cluster
+  __shared__ int32_t s_bw[EXT ? DP * DP : 1], s_lat[EXT ? DP * DP : 1];
+  __shared__ double s_inv[EXT ? DP * DP : 1];
+  // out-edges of a cluster of at most kSucc of them (ob, count), for back_cost
+  // under link tables (the tables of 64 devices leave no room for them)
+  constexpr int kSucc = EXT && DP <= 32 ? 64 : 0;
+  __shared__ PlNear s_succ[kSucc ? 2 : 1][kSucc ? kPlB : 1][kSucc ? kSucc : 1];
+  __shared__ int s_f;
+  if (threadIdx.x == 0) s_f = failed(st) ? 1 : 0;
+  __syncthreads();
+  if (s_f) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t C = a.C, D = a.D;
-  const bool mine = lane < D;
-  if (a.links)
-    for (int i = lane; i < D * D; i += 64) {
+  const bool links = EXT && a.links;
+  if (threadIdx.x <= kPlRing) s_ring[threadIdx.x] = PlFin{0, 0};
+  if (links)
+    for (int i = threadIdx.x; i < D * D; i += blockDim.x) {
       s_bw[i] = (int32_t)a.lbw[i];
       s_lat[i] = (int32_t)a.llat[i];
+      s_inv[i] = 1.0 / (double)a.lbw[i];
     }
-  lds_order();
-  wave_lds_sync();
-  int64_t ava = mine ? a.cap[lane] : 0;
-  int32_t nb = 0;
-  int64_t lastb = 0;
-  int64_t *xs = a.bs + (int64_t)(mine ? lane : 0) * a.bcap, *xf = a.bf + (int64_t)(mine ? lane : 0) * a.bcap;
-  int32_t prev = 0, be = 0;
-  int64_t span = 0;
-  auto finof = [&](int32_t c) -> int64_t { return LDSF ? s_fin[c] : a.Fin[c]; };
-  auto devof = [&](int32_t c) -> int32_t { return LDSF ? (int32_t)s_cd[c] : (int32_t)a.cdev[c]; };
-  for (int32_t t = 0; t < C; t++) {
-    // followers of earlier groups: their memory on their leading device
-    const int32_t f0 = a.foff[t], f1 = a.foff[t + 1];
-    for (int32_t k0 = f0; k0 < f1; k0 += 64) {
-      const int32_t k = k0 + lane;
-      int32_t fd = -1;
-      int64_t fmv = 0;
-      if (k < f1) {
-        fd = devof(a.fl[k]);
-        fmv = a.fm[k];
-      }
-      const int nk = f1 - k0 < 64 ? f1 - k0 : 64;
-      for (int j = 0; j < nk; j++) {
-        const int32_t dj = __builtin_amdgcn_readlane(fd, j);
-        const int64_t mj = readlane64(fmv, j);
-        if (lane == dj) ava -= mj;
-      }
-    }
-    const int64_t Mt = (int64_t)a.MEMo[t];
-    const int64_t Wx = mine ? (int64_t)a.W2[(int64_t)t * D + lane] : 0;
-    // pre_t on device `lane` (eq. 7)
-    int64_t pre = 0;
+  __syncthreads();
+
+  // helper: cluster j of batch kb; the clusters before F = kPlB (kb - 1) are
+  // final, those of batch kb - 2 in the ring, earlier ones in global memory
+  constexpr int P = 64 / DP;
+  const int x = lane & (DP - 1), grp = lane / DP;
+  const int xd = x < D ? x : 0;
+  auto prepare = [&](int32_t kb, int j) {
+    const int32_t t = kb * kPlB + j;
+    if (t >= C) return;
+    const int buf = kb & 1;
+    const int32_t F = kPlB * (kb - 1), Fr = F - kPlB;  // clusters [Fr, F): in the ring
     const int32_t b0 = a.boff[t], np = a.ncp[t];
+    // finish time and device of a cluster before F
+    auto done = [&](int32_t c, int64_t &f, int32_t &d) {
+      if (c >= Fr) {
+        f = s_ring[c & (kPlRing - 1)].fin;
+        d = (int32_t)s_ring[c & (kPlRing - 1)].dev;
+      } else {
+        f = a.Fin[c];
+        d = a.cdev[c];
+      }
+    };
+    int64_t pre = 0;
+    int32_t nn = 0;
     for (int32_t k0 = 0; k0 < np; k0 += 64) {
       const int32_t k = k0 + lane;
-      int64_t pf = 0, pc = 0, po = 0, pn = 0;
-      int32_t pd = 0;
-      if (k < np) {
-        const int32_t pa = a.ca[b0 + k];
-        pf = finof(pa);
-        pd = devof(pa);
-        pc = a.cc[b0 + k];
-        if (a.links) {
-          po = a.cob[b0 + k];
-          pn = a.cnum[b0 + k];
-        }
+      const bool in = k < np;
+      int32_t src = 0, d = 0;
+      int64_t f = 0, c = 0, num = 0;
+      if (in) {
+        src = a.ca[b0 + k];
+        c = links ? a.cob[b0 + k] : a.cc[b0 + k];
+        if (links) num = a.cnum[b0 + k];
+        if (src < F) done(src, f, d);
       }
-      const int nk = np - k0 < 64 ? np - k0 : 64;
-      for (int j = 0; j < nk; j++) {
-        const int64_t fj = readlane64(pf, j);
-        const int32_t dj = __builtin_amdgcn_readlane(pd, j);
+      const uint64_t nm = __ballot(in && src >= F);
+      if (in && src >= F)
+        s_near[buf][j][nn + __popcll(nm & ((1ull << lane) - 1))] =
+            PlNear{c, ((int64_t)(src & (kPlRing - 1)) << 32) | num};
+      nn += __popcll(nm);
+      const int nf = __popcll(__ballot(in && src < F));  // a prefix of the lanes
+      for (int e0 = 0; e0 < nf; e0 += P) {
+        const int e = e0 + grp;
+        const int el = e < 64 ? e : 63;
+        const int64_t fe = __shfl(f, el), ce = __shfl(c, el);
+        const int32_t de = __shfl(d, el);
         int64_t cost = 0;
-        if (dj != lane) {
-          if (a.links)
-            cost = link_cost(readlane64(po, j), readlane64(pn, j), s_bw[dj * D + (mine ? lane : 0)],
-                             s_lat[dj * D + (mine ? lane : 0)]);
-          else
-            cost = readlane64(pc, j);
+        if (links) {
+          const int64_t ne = __shfl(num, el);
+          if (de != x) {
+            const int li = de * D + xd;
+            cost = link_cost_inv(ce, ne, s_bw[li], s_lat[li], s_inv[li]);
+          }
+        } else if (de != x) {
+          cost = ce;
         }
-        pre = fj + cost > pre ? fj + cost : pre;
+        if (e < nf && fe + cost > pre) pre = fe + cost;
       }
     }
-    // first fit on device `lane`
-    int64_t sv = pre;
-    if (mine && Wx > 0 && nb > 0 && sv < lastb)
-      for (int32_t q = blocks_ending_by(xf, nb, sv); q < nb && xs[q] < sv + Wx; q++) sv = xf[q];
-    const int64_t eft = (mine && ava >= Mt) ? sv + Wx : kInf;
-    // best device (lowest id on ties)
-    int64_t ev = eft;
-    int32_t ei = lane;
-    for (int off = 32; off > 0; off >>= 1) {
-      const int64_t ov = __shfl_xor((long long)ev, off);
-      const int32_t oi = __shfl_xor(ei, off);
-      if (ov < ev || (ov == ev && oi < ei)) {
-        ev = ov;
-        ei = oi;
+    pre = copies_max<DP>(pre);
+    s_pre[buf][j][lane] = pre;
+    // the padding to a multiple of P (P at least): a source that finished at 0, at no cost
+    if (lane < P && nn + lane < (nn > 0 ? (nn + P - 1) / P * P : P))
+      s_near[buf][j][nn + lane] = PlNear{0, (int64_t)kPlRing << 32};
+    if (lane == 0) {
+      s_hdr[buf][j][0] = EXT ? 0 : (int64_t)a.W[t];
+      s_hdr[buf][j][1] = (int64_t)a.MEM[t];
+      s_hdr[buf][j][2] = links ? (int64_t)(a.soff[t + 1] - a.soff[t]) : (int64_t)a.back[t];
+      s_hdr[buf][j][3] = nn;
+    }
+    if (kSucc > 0 && links) {
+      const int32_t k = a.soff[t] + lane;
+      if (k < a.soff[t + 1] && lane < kSucc) s_succ[buf][j][lane] = PlNear{a.sob[k], a.snum[k]};
+    }
+    if (EXT) {
+      s_wx[buf][j][lane] = (int64_t)a.W[(int64_t)t * a.U + a.uidx[xd]];
+      s_fol[buf][j][lane] = 0;
+      if (lane < kPlNear) s_folw[buf][j][lane] = 0;
+      wave_lds_sync();
+      if (a.foff)
+        for (int32_t k = a.foff[t] + lane; k < a.foff[t + 1]; k += 64) {
+          const int32_t l = a.fl[k];
+          int64_t f;
+          int32_t d;
+          if (l < F) {
+            done(l, f, d);
+            atomicAdd((unsigned long long *)&s_fol[buf][j][d], (unsigned long long)a.fm[k]);
+          } else {
+            atomicAdd((unsigned long long *)&s_folw[buf][j][l - F], (unsigned long long)a.fm[k]);
+          }
+        }
+    }
+  };
+
+  // ---- wave 0's state of device x
+  const bool act = x < D;
+  const int32_t capL = kBlk / D;
+  int64_t ava = act ? a.cap[xd] : 0;
+  int64_t last = 0, lst = 0, pend = 0;  // end and start of its last block, end of the one before
+  int32_t nb = 0, glob = 0;             // blocks; list moved to global memory
+  int32_t prev = 0, be = 0;
+  int64_t span = 0;                     // largest finish on the device
+  auto list_s = [&]() { return glob ? a.bs + (int64_t)xd * a.bcap : s_bs + xd * capL; };
+  auto list_f = [&]() { return glob ? a.bf + (int64_t)xd * a.bcap : s_bf + xd * capL; };
+  auto flush = [&]() {  // the last block's end into the list
+    if (lane < D && nb > 0) list_f()[nb - 1] = last;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  };
+  struct Pre {  // one cluster's prepared values
+    int64_t w, m, bk, pre, fol, fw;
+    int32_t nn;
+    PlNear e;
+  };
+  auto load = [&](int buf, int j) {
+    Pre p;
+    p.e = s_near[buf][j][grp];
+    p.w = EXT ? s_wx[buf][j][lane] : s_hdr[buf][j][0];
+    p.m = s_hdr[buf][j][1];
+    p.bk = s_hdr[buf][j][2];
+    p.nn = (int32_t)s_hdr[buf][j][3];
+    p.pre = s_pre[buf][j][lane];
+    p.fol = EXT ? s_fol[buf][j][x] : 0;
+    p.fw = EXT ? s_folw[buf][j][lane & (kPlNear - 1)] : 0;
+    return p;
+  };
+  // places cluster t (cluster j of its batch) and returns the values of cluster jn
+  auto place = [&](int32_t t, int buf, int j, const Pre &p, int jn) -> Pre {
+    const int32_t nn = __builtin_amdgcn_readfirstlane(p.nn);
+    const int64_t w = p.w, m = p.m;
+    // ---- pre_t: the near in-edges, P at a time
+    auto near_val = [&](const PlNear &e, const PlFin &r) -> int64_t {
+      int64_t c = e.c;
+      if (links) {
+        const int li = (int32_t)r.dev * D + xd;
+        c = link_cost_inv(c, (int64_t)(uint32_t)e.sn, s_bw[li], s_lat[li], s_inv[li]);
+      }
+      return r.fin + ((int32_t)r.dev == x ? 0 : c);
+    };
+    const PlFin r0 = s_ring[(int32_t)(p.e.sn >> 32)];
+    lds_order();
+    const Pre next = load(buf, jn);  // behind the read this step waits for
+    lds_order();
+    int64_t nv = near_val(p.e, r0);
+    for (int32_t e0 = P; e0 < nn; e0 += P) {
+      const PlNear e = s_near[buf][j][e0 + grp];
+      nv = max_nonneg(nv, near_val(e, s_ring[(int32_t)(e.sn >> 32)]));
+    }
+    const int64_t sv = copies_max<DP>(max_nonneg(nv, p.pre));
+    if (EXT) {  // followers of earlier groups: their memory on their leading device
+      ava -= p.fol;
+      for (uint64_t mk = __ballot(lane < kPlNear && p.fw != 0); mk; mk &= mk - 1) {
+        const int i = __builtin_ctzll(mk);
+        const int32_t l = (t / kPlB - 1) * kPlB + i;
+        if (x == (int32_t)s_ring[l & (kPlRing - 1)].dev) ava -= readlane64(p.fw, i);
       }
     }
-    const int32_t dk = t == 0 ? 0 : prev;
-    const int64_t edk = readlane64(eft, dk);
-    int32_t pick;
-    if (ev == kInf) {  // every device full: most remaining memory (best effort)
-      int64_t av = mine ? ava : INT64_MIN;
-      int32_t ai = mine ? lane : INT32_MAX;
-      argmax_i64(av, ai);
-      pick = ai;
-      be++;
-    } else if (edk == kInf || ei == dk) {
-      pick = ei;
-    } else {
-      int64_t bk = 0;  // back_cost (eq. 8)
-      if (!a.links) {
-        bk = (int64_t)a.back[t];
-      } else {
-        const int32_t bw = s_bw[ei * D + dk], lt = s_lat[ei * D + dk];
-        for (int32_t k = a.soff[t] + lane; k < a.soff[t + 1]; k += 64) {
-          const int64_t c = link_cost(a.sob[k], a.snum[k], bw, lt);
-          bk = c > bk ? c : bk;
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-          const int64_t o = __shfl_xor((long long)bk, off);
-          bk = o > bk ? o : bk;
+    // ---- first-fit start on device x (last = 0 while it has no block)
+    const bool busy = w > 0 && sv < last;
+    int64_t s = busy && sv + w > lst ? last : sv;  // exact when sv >= pend
+    if (__ballot(busy && sv < pend)) {  // an earlier gap may hold it
+      flush();
+      if (busy && sv < pend) {
+        const int64_t *xs = list_s(), *xf = list_f();
+        s = sv;
+        for (int32_t k = blocks_ending_by(xf, nb, s); k < nb && xs[k] < s + w; k++) s = xf[k];
+      }
+    }
+    // ---- the device (eq. 7-9): compared on the start (EXT: on the finish)
+    const int64_t f = s + w, key = EXT ? f : s;
+    const uint64_t feas = __ballot(act && ava >= m);
+    int32_t pick = prev;
+    const int64_t kp = readlane64(key, prev);
+    const uint64_t better =
+        __ballot(key < (links ? kp : kp - readlane64(p.bk, 0))) & feas;
+    if (better != 0 || !((feas >> prev) & 1)) {
+      if (feas == 0) {  // every device full: most remaining memory (best effort)
+        int64_t av = act ? ava : INT64_MIN;  // can be negative after best-effort picks
+        int32_t ai = act ? x : INT32_MAX;
+        argmax_i64(av, ai);
+        pick = __builtin_amdgcn_readfirstlane(ai);
+        be++;
+      } else {  // the smallest, lowest id on ties
+        const int64_t est = act && ava >= m ? key : kPlaceFull;
+        const int64_t red = kPlaceFull - est;  // so that the reduction's identity is 0
+        const int64_t ev = kPlaceFull - (DP == 16 ? wave_max_nonneg<false>(red) : wave_max_nonneg<true>(red));
+        const int32_t ei = (int32_t)__builtin_ctzll(__ballot(est == ev));
+        pick = ei;
+        if (links && ((feas >> prev) & 1)) {  // back_cost (eq. 8) on the link back
+          const int li = ei * D + prev;
+          const int32_t ns = (int32_t)p.bk;
+          int64_t bk = 0;
+          if (kSucc > 0 && ns <= kSucc) {
+            const PlNear e = s_succ[buf][j][lane < kSucc ? lane : 0];
+            if (lane < ns) bk = link_cost_inv(e.c, e.sn, s_bw[li], s_lat[li], s_inv[li]);
+          } else {
+            for (int32_t k = a.soff[t] + lane; k < a.soff[t + 1]; k += 64) {
+              const int64_t c = link_cost_inv(a.sob[k], a.snum[k], s_bw[li], s_lat[li], s_inv[li]);
+              bk = c > bk ? c : bk;
+            }
+          }
+          bk = wave_max_nonneg<true>(bk);
+          if (kp - ev <= bk) pick = prev;
         }
       }
-      pick = edk - ev > bk ? ei : dk;
     }
-    const int64_t s0 = readlane64(sv, pick), wp = readlane64(Wx, pick), f = s0 + wp;
-    span = f > span ? f : span;
     prev = pick;
-    if (lane == pick) {
-      if (wp > 0) lastb = busy_insert(xs, xf, nb, a.bcap, s0, f, st);
-      ava -= Mt;
-    }
-    if (lane == 0) {  // later steps of this wave read these back, in program order
-      a.cdev[t] = (uint8_t)pick;
-      a.Fin[t] = f;
-      if (LDSF) {
-        s_fin[t] = f;
-        s_cd[t] = (uint8_t)pick;
+    // ---- [s, f) into the device's busy blocks
+    const bool mine = x == pick;
+    if (__ballot(mine && w > 0 && (s != last || nb == 0))) {  // not at the last block's end
+      flush();
+      const int32_t nbp = __builtin_amdgcn_readlane(nb, pick);
+      if (!__builtin_amdgcn_readlane(glob, pick) && nbp == capL) {
+        for (int32_t q = lane; q < nbp; q += 64) {  // the LDS share is full: to global memory
+          a.bs[(int64_t)pick * a.bcap + q] = s_bs[pick * capL + q];
+          a.bf[(int64_t)pick * a.bcap + q] = s_bf[pick * capL + q];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        if (mine) glob = 1;
       }
+      if (lane == pick) {
+        int64_t *xs = list_s(), *xf = list_f();
+        if (nb == 0 || s > last) {  // a new block at the end
+          xs[nb] = s;
+          pend = last;
+          lst = s;
+          last = f;
+          nb++;
+        } else {  // into an idle gap
+          last = busy_insert(xs, xf, nb, glob ? a.bcap : capL, s, f, st);
+          lst = xs[nb - 1];
+          pend = nb > 1 ? xf[nb - 2] : 0;
+        }
+      }
+      if (P > 1) {  // the other copies follow
+        const int64_t l2 = readlane64(last, pick), s2 = readlane64(lst, pick), p2 = readlane64(pend, pick);
+        const int32_t n2 = __builtin_amdgcn_readlane(nb, pick);
+        if (mine) {
+          last = l2;
+          lst = s2;
+          pend = p2;
+          nb = n2;
+        }
+      }
+    } else if (mine && w > 0) {
+      last = f;  // extends the last block
     }
-    if (LDSF) lds_order();
+    if (mine) {
+      s_ring[t & (kPlRing - 1)] = PlFin{f, pick};
+      ava -= m;
+      span = max_nonneg(span, f);
+    }
+    lds_order();
+    return next;
+  };
+
+  const int32_t nbat = (C + kPlB - 1) / kPlB;
+  if (wave > 0) prepare(0, wave - 1);
+  else __builtin_amdgcn_s_setprio(3);
+  __syncthreads();
+  for (int32_t k = 0; k < nbat; k++) {
+    const int32_t t0 = k * kPlB, nt = C - t0 < kPlB ? C - t0 : kPlB;
+    if (wave == 0) {
+      Pre p = load(k & 1, 0);
+      for (int32_t j = 0; j < nt; j++) p = place(t0 + j, k & 1, j, p, j + 1 < nt ? j + 1 : j);
+    } else {
+      if (wave == 1 && k > 0 && lane < kPlB) {  // batch k - 1 into global memory, read from batch k + 1 on
+        const PlFin r = s_ring[(t0 - kPlB + lane) & (kPlRing - 1)];
+        a.Fin[t0 - kPlB + lane] = r.fin;
+        a.cdev[t0 - kPlB + lane] = (uint8_t)r.dev;
+      }
+      prepare(k + 1, wave - 1);
+    }
+    __syncthreads();
   }
-  if (lane == 0) {
-    st->s0 = span;
-    st->i0 = be;
+  if (wave == 1 && lane < C - (nbat - 1) * kPlB) {
+    const int32_t t = (nbat - 1) * kPlB + lane;
+    a.Fin[t] = s_ring[t & (kPlRing - 1)].fin;
+    a.cdev[t] = (uint8_t)s_ring[t & (kPlRing - 1)].dev;
   }
+  if (wave == 0) {
+    span = wave_max_nonneg<true>(span);
+    if (lane == 0) {
+      st->s0 = span;
+      st->i0 = be;
+    }
+  }
+}
+
+template <bool EXT>
+static void place_ahead(const PlaceArgs &a, Status *st, hipStream_t s) {
+  if (a.D <= 16) k_place_ahead<EXT, 16><<<1, 64 * (kPlB + 1), 0, s>>>(a, st);
+  else if (a.D <= 32) k_place_ahead<EXT, 32><<<1, 64 * (kPlB + 1), 0, s>>>(a, st);
+  else k_place_ahead<EXT, 64><<<1, 64 * (kPlB + 1), 0, s>>>(a, st);
 }
 
 // node_dev: a group member takes its leading cluster's device, every other
@@ -1039,29 +1300,47 @@ extern "C" int cel_place(const cel_graph *g, const cel_devices *d, const int32_t
   CEL_TRY(segmented_sort(keys, ids, boff, C, ncross, sc, s, st));
   k_place_combine<<<grid_for((int64_t)C * 64, 256, 8192), 256, 0, s>>>(C, boff, keys, ids, ecost,
                                                                       ca, cc, ncp, back, st);
-  // Busy lists in LDS only first; if one outgrows its share (st->i1 set, the
-  // outputs not written), the placement again with lists that move to global
-  // memory when full.
-  for (int gl = 0; gl < 2; gl++) {
+  if (d->D <= 64) {  // one lane per device
+    PlaceArgs pa{};
+    pa.C = C;
+    pa.D = d->D;
+    pa.cap = dcap;
+    pa.W = W;
+    pa.MEM = MEM;
+    pa.boff = boff;
+    pa.ncp = ncp;
+    pa.ca = ca;
+    pa.cc = cc;
+    pa.back = back;
+    pa.cdev = cluster_dev;
+    pa.Fin = Fin;
+    pa.bs = bs;
+    pa.bf = bf;
+    pa.bcap = (int32_t)bcap;
     {
       KTimer kt(s, "k_place");
-#define CEL_PLACE_LAUNCH(LDSF, GL, NI)                                                          \
-  k_place<LDSF, GL, NI><<<1, 64, 0, s>>>(C, d->D, dcap, W, MEM, boff, ncp, ca, cc, back,        \
-                                         cluster_dev, Fin, bs, bf, (int32_t)bcap, st)
-      const bool lds = C <= kPlaceLds, one = d->D <= 64;
-      if (lds && !gl) {
-        if (one) CEL_PLACE_LAUNCH(true, false, 1);
-        else CEL_PLACE_LAUNCH(true, false, 4);
-      } else if (lds) {
-        if (one) CEL_PLACE_LAUNCH(true, true, 1);
-        else CEL_PLACE_LAUNCH(true, true, 4);
-      } else if (!gl) {
-        if (one) CEL_PLACE_LAUNCH(false, false, 1);
-        else CEL_PLACE_LAUNCH(false, false, 4);
-      } else {
-        if (one) CEL_PLACE_LAUNCH(false, true, 1);
-        else CEL_PLACE_LAUNCH(false, true, 4);
-      }
+      place_ahead<false>(pa, st, s);
+    }
+    k_place_out<<<grid_for(n > C ? n : C, 256, 4096), 256, 0, s>>>(n, C, cluster_id, cluster_dev,
+                                                                  node_dev, Fin, cluster_fin, st);
+    CEL_HIP(hipGetLastError());
+    CEL_TRY(read_status(st, &h, s));
+    if (h.err) return status_error(h, fn);
+  }
+  // More devices than lanes: busy lists in LDS only first; if one outgrows its
+  // share (st->i1 set, the outputs not written), the placement again with
+  // lists that move to global memory when full.
+  for (int gl = d->D <= 64 ? 2 : 0; gl < 2; gl++) {
+    {
+      KTimer kt(s, "k_place");
+#define CEL_PLACE_LAUNCH(LDSF, GL)                                                              \
+  k_place<LDSF, GL, 4><<<1, 64, 0, s>>>(C, d->D, dcap, W, MEM, boff, ncp, ca, cc, back,         \
+                                        cluster_dev, Fin, bs, bf, (int32_t)bcap, st)
+      const bool lds = C <= kPlaceLds;
+      if (lds && !gl) CEL_PLACE_LAUNCH(true, false);
+      else if (lds) CEL_PLACE_LAUNCH(true, true);
+      else if (!gl) CEL_PLACE_LAUNCH(false, false);
+      else CEL_PLACE_LAUNCH(false, true);
 #undef CEL_PLACE_LAUNCH
     }
     k_place_out<<<grid_for(n > C ? n : C, 256, 4096), 256, 0, s>>>(n, C, cluster_id, cluster_dev,
@@ -1198,12 +1477,26 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
   }
   const bool grp = n_groups > 0;
   const int64_t m = g->m, bcap = C;
+  // each device's speed as an index into the distinct ones
+  std::vector<int64_t> umul;
+  std::vector<int32_t> uidx(D, 0);
+  for (int32_t x = 0; x < D; x++) {
+    const int64_t tm = het && h->tmul ? h->tmul[x] : 1024;
+    size_t u = 0;
+    while (u < umul.size() && umul[u] != tm) u++;
+    if (u == umul.size()) umul.push_back(tm);
+    uidx[x] = (int32_t)u;
+  }
+  const int32_t U = (int32_t)umul.size();
   uint64_t *W2, *MEMo, *back, *keys;
+  int32_t *uidx_d;
   int32_t *cnt, *boff, *ca, *ncp, *lead, *fcnt, *foff, *fl, *soff, *scnt;
-  int64_t *ecost, *eob, *eone, *cc, *cob, *cnum, *Fin, *bs, *bf, *dcap, *tm_d = nullptr, *fm;
+  int64_t *ecost, *eob, *eone, *cc, *cob, *cnum, *Fin, *bs, *bf, *dcap, *umul_d, *fm;
   int64_t *sob = nullptr, *snum = nullptr, *lbw = nullptr, *llat = nullptr;
   uint32_t *ids;
-  CEL_TRY(sc.get(&W2, (int64_t)C * D));
+  CEL_TRY(sc.get(&W2, (int64_t)C * U));
+  CEL_TRY(sc.get(&umul_d, U));
+  CEL_TRY(sc.get(&uidx_d, D));
   CEL_TRY(sc.get(&MEMo, C));
   CEL_TRY(sc.get(&back, C));
   CEL_TRY(sc.get(&cnt, C));
@@ -1218,18 +1511,15 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
   CEL_TRY(sc.get(&foff, (int64_t)C + 1));
   CEL_TRY(sc.get(&soff, (int64_t)C + 1));
   CEL_TRY(sc.get(&scnt, C));
-  CEL_HIP(hipMemsetAsync(W2, 0, sizeof(uint64_t) * C * D, s));
+  CEL_HIP(hipMemsetAsync(W2, 0, sizeof(uint64_t) * C * U, s));
   CEL_HIP(hipMemsetAsync(MEMo, 0, sizeof(uint64_t) * C, s));
   CEL_HIP(hipMemsetAsync(back, 0, sizeof(uint64_t) * C, s));
   CEL_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * C, s));
   CEL_HIP(hipMemsetAsync(fcnt, 0, sizeof(int32_t) * C, s));
   CEL_HIP(hipMemcpyAsync(dcap, d->cap, sizeof(int64_t) * D, hipMemcpyHostToDevice, s));
-  std::vector<int64_t> ht, hb, hl;
-  if (het && h->tmul) {
-    CEL_TRY(sc.get(&tm_d, D));
-    ht.assign(h->tmul, h->tmul + D);
-    CEL_HIP(hipMemcpyAsync(tm_d, ht.data(), sizeof(int64_t) * D, hipMemcpyHostToDevice, s));
-  }
+  std::vector<int64_t> hb, hl;
+  CEL_HIP(hipMemcpyAsync(umul_d, umul.data(), sizeof(int64_t) * U, hipMemcpyHostToDevice, s));
+  CEL_HIP(hipMemcpyAsync(uidx_d, uidx.data(), sizeof(int32_t) * D, hipMemcpyHostToDevice, s));
   if (links) {
     CEL_TRY(sc.get(&lbw, (int64_t)D * D));
     CEL_TRY(sc.get(&llat, (int64_t)D * D));
@@ -1250,8 +1540,8 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
     k_colo_lead<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, n_groups, group, cluster_id,
                                                       grp ? lead : nullptr, st);
   }
-  k_pe_nodes<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, C, D, cluster_id, g->w, g->mem,
-                                                    grp ? group : nullptr, lead, tm_d, W2, MEMo,
+  k_pe_nodes<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, C, U, cluster_id, g->w, g->mem,
+                                                    grp ? group : nullptr, lead, umul_d, W2, MEMo,
                                                     fcnt, st);
   CEL_TRY(exclusive_scan_i32(fcnt, foff, C, sc, s));
   const unsigned eb = edge_blocks(g->m);
@@ -1310,13 +1600,15 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
     k_pe_succ<1><<<grid_for(C, 256, 4096), 256, 0, s>>>(C, boff, ncp, ca, cob, cnum, scnt, soff,
                                                        sob, snum, st);
   }
-  PeArgs pa{};
+  PlaceArgs pa{};
   pa.C = C;
   pa.D = D;
   pa.links = links;
   pa.cap = dcap;
-  pa.W2 = W2;
-  pa.MEMo = MEMo;
+  pa.W = W2;
+  pa.MEM = MEMo;
+  pa.uidx = uidx_d;
+  pa.U = U;
   pa.boff = boff;
   pa.ncp = ncp;
   pa.ca = ca;
@@ -1327,7 +1619,7 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
   pa.soff = soff;
   pa.sob = sob;
   pa.snum = snum;
-  pa.foff = foff;
+  pa.foff = nfol > 0 ? foff : nullptr;
   pa.fl = fl;
   pa.fm = fm;
   pa.lbw = lbw;
@@ -1339,8 +1631,7 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
   pa.bcap = (int32_t)bcap;
   {
     KTimer kt(s, "k_place_ext");
-    if (C <= kPeLds) k_place_ext<true><<<1, 64, 0, s>>>(pa, st);
-    else k_place_ext<false><<<1, 64, 0, s>>>(pa, st);
+    place_ahead<true>(pa, st, s);
   }
   k_pe_out<<<grid_for(n > C ? n : C, 256, 4096), 256, 0, s>>>(n, C, cluster_id,
                                                              grp ? group : nullptr, lead,
