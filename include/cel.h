@@ -364,7 +364,7 @@ int cel_topo_levels_info(int32_t *info);
 
 /* Diagnostics: how the calling thread's last cel_cluster call ran the DP
  * (mode CEL_CLUSTER_DP).  info[0] = 0: by policy iteration over the back
- * pointers (graphs of 16,384 nodes and more), exact after info[1]
+ * pointers (graphs of 3,072 nodes and more), exact after info[1]
  * iterations; 1: by the blocked sequential DP (after info[1] iterations that
  * did not converge within their budget, or 0 when policy iteration was not
  * tried).
