@@ -671,6 +671,35 @@ int mb_ring(int32_t K, int32_t n, int32_t m, int32_t L, const int32_t *lp, const
             const int32_t *level, const int32_t *pptr, const int32_t *pidx, const int64_t *wp,
             const int64_t *cq, const uint8_t *devp, int64_t *fin, int64_t *fc, int64_t *makespan,
             class Scratch &sc, hipStream_t s, Status *st);
+// ms_blocks.hip: finish times (finp [K][n] by position) and makespans of K
+// placements without insertion, in blocks of tasks.  aoff (offsets of every
+// position's transfers, [K n + 1]) and dmask (its destination devices) make
+// the transfers tasks (block: on the compute queues, else on channels); without
+// them a cross-device input costs cq.  tmul / lbw / llat (all or none):
+// heterogeneous devices, cq then holds ob.  st->i1 = 1 when values may reach
+// 2^47 (fits: known not to) or a placement needs more than budget iterations:
+// nothing is written then and the caller takes its other method.
+// K <= kBkMaxK, n * K + transfers <= kBkMaxTasks.
+constexpr int32_t kBkMaxK = 65535;
+constexpr int64_t kBkMaxTasks = int64_t(1) << 28;  // 38 bytes of scratch each
+struct MsBlocks {
+  int32_t K, n, D, budget, fits;
+  bool block;
+  const int32_t *iptr, *iidx;
+  const int4 *ipre;             // k_mm_ipre
+  const int64_t *wp, *cq;
+  const uint8_t *devp;
+  const int64_t *tmul, *lbw, *llat;
+  const int64_t *aoff;
+  const uint64_t *dmask;
+  int64_t transfers;
+  int64_t *finp, *makespan;
+  const char *timer;
+};
+int ms_blocks(const MsBlocks &b, class Scratch &sc, hipStream_t s, Status *st);
+// makespan_model.hip: first 4 inputs of each position (-1 past the row's end)
+__global__ void k_mm_ipre(int32_t n, const int32_t *iptr, const int32_t *iidx, int4 *ipre,
+                          const Status *st);
 // ms_wide.hip: makespans of K placements over a level-grouped priority order
 // whose levels are wide (positions as for mb_ring; 1 <= D <= kWDev,
 // n <= kWMaxN); fin [K][n], makespan [K]

@@ -6,6 +6,8 @@
 // holds one of its successors, in increasing device order, occupying the
 // producer device's send channel and the target device's receive channel.
 //
+// Without insertion most calls take blocks of tasks (ms_blocks.hip); the rest:
+//
 // Under either model a node's start depends on everything placed before it on
 // its device, so a placement is a walk in order.  One wave walks one
 // placement, 64 consecutive positions (a window) at a time:
@@ -49,6 +51,12 @@
 
 namespace cel {
 
+// Smaller graphs are walked in order: the blocks' extra launches cost more.
+// Whole calls, walk against blocks: transfer tasks 288 / 230 us at 1,024 nodes
+// (K = 300: 347 / 302) and 253 / 250 at 640; FIFO devices 700 / 250 us at 4,169
+// and 245 / 172 at 2,048, but 236 / 242 there with K = 300 (a walk takes a wave,
+// blocks a workgroup).
+constexpr int32_t kMmBlocksXfer = 1024, kMmBlocksFifo = 4096;
 constexpr int kMmLight = 16;  // rows with more inputs are folded by the whole wave
 
 struct MmArgs {
@@ -891,7 +899,7 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
   const bool ins = model & CEL_MODEL_INSERT, tasks = model & CEL_MODEL_COMM_TASKS;
   const bool block = model & CEL_MODEL_COMM_BLOCK;
   const bool het = h && (h->tmul || h->bw || h->lat);
-  int64_t bwmin = d->bw, latmax = d->lat, tmax = 1024;
+  int64_t bwmin = d->bw, latmax = d->lat, tmax = 1024, worst_total = 0;
   if (het) {
     CEL_TRY(check_hetero(h, d, fn, &bwmin, &latmax, &tmax));
     // overflow bound with the slowest device and the worst link: every time
@@ -904,6 +912,7 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
     const __int128 tot = (__int128)ws * ((tmax + 1023) / 1024) + ec;
     if (tot >= ((__int128)1 << 62))
       return set_error(CEL_E_OVERFLOW, "%s: times could reach 2^62", fn);
+    worst_total = (int64_t)tot;
   }
   Scratch sc(s);
   Status *st;
@@ -986,9 +995,10 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
     a.ga = ga;
     a.gb = gb;
   }
+  int64_t total = 0;  // transfers of all placements (valid once the checks passed)
   if (tasks || block) {
     uint64_t *dmask;
-    int64_t *pc, *aoff, *pool;
+    int64_t *pc, *aoff;
     CEL_TRY(sc.get(&dmask, Kn));
     CEL_TRY(sc.get(&pc, Kn));
     CEL_TRY(sc.get(&aoff, Kn + 1));
@@ -997,16 +1007,56 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
                                                            (unsigned long long *)dmask, st);
     k_mm_popc<<<grid_for(Kn, 256, 8192), 256, 0, s>>>(Kn, dmask, pc, st);
     CEL_TRY(exclusive_scan_i64(pc, aoff, Kn, sc, s));
-    int64_t total = 0;  // transfers of all placements (valid once the checks passed)
     CEL_HIP(hipMemcpyAsync(&total, aoff + Kn, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     Status h0;
     CEL_TRY(read_status(st, &h0, s));
     if (h0.err) return status_error(h0, fn);
-    CEL_TRY(sc.get(&pool, total > 0 ? total : 1));
     a.dmask = dmask;
     a.aoff = aoff;
-    a.pool = pool;
   }
+  // Without insertion every start is fixed by the order: blocks of tasks in
+  // LDS.  The walk below when values may need more than 47 bits, when the
+  // blocks need more iterations (about 1.2 us each) than the walk takes (42 ns
+  // a node under FIFO devices, 117 with transfers, 208 with transfers on the
+  // compute queues), and for graphs of so few nodes that it takes less than the
+  // blocks' extra launches.
+  if (!ins && n >= (tasks || block ? kMmBlocksXfer : kMmBlocksFifo) && K <= kBkMaxK && Kn + total <= kBkMaxTasks &&
+      (!het || worst_total < (int64_t(1) << 47))) {
+    const Scratch::Mark mk = sc.mark();
+    MsBlocks b{};
+    b.K = K;
+    b.n = n;
+    b.D = D;
+    b.budget = 64 + (int32_t)((block ? 0.17 : tasks ? 0.1 : 0.035) * n);
+    b.fits = het ? 1 : 0;
+    b.block = block;
+    b.iptr = iptr;
+    b.iidx = iidx;
+    b.ipre = ipre;
+    b.wp = wp;
+    b.cq = cq;
+    b.devp = devp;
+    b.tmul = tmul_d;
+    b.lbw = a.lbw;
+    b.llat = a.llat;
+    b.aoff = a.aoff;
+    b.dmask = a.dmask;
+    b.transfers = total;
+    b.finp = finp;
+    b.makespan = makespan;
+    b.timer = "k_makespan_model";
+    CEL_TRY(ms_blocks(b, sc, s, st));
+    if (start || finish)
+      k_mm_out<<<grid_for(Kn, 256, 8192), 256, 0, s>>>(K, n, order, finp, wp, devp, tmul_d, start,
+                                                      finish, st);
+    CEL_HIP(hipGetLastError());
+    Status hb;
+    CEL_TRY(read_status(st, &hb, s));
+    if (hb.err) return status_error(hb, fn);
+    if (!hb.i1) return CEL_OK;
+    sc.release(mk);
+  }
+  if (tasks || block) CEL_TRY(sc.get(&a.pool, total > 0 ? total : 1));
   {
     KTimer kt(s, "k_makespan_model");
     const unsigned gk = (unsigned)K;
