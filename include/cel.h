@@ -357,7 +357,7 @@ int cel_blevel_info(int32_t *info);
  * levels.  info[0] = 0: by policy iteration over the predecessors (graphs of
  * 16,384 nodes and more), exact after info[1] iterations; 1: by Kahn's
  * level-synchronous kernel (after info[1] iterations that did not converge
- * within their budget of 12, or 0 when policy iteration was not tried).
+ * within their budget, or 0 when policy iteration was not tried).
  * Outputs: info [2] (host).
  * Errors: CEL_E_ARG (NULL argument). */
 int cel_topo_levels_info(int32_t *info);

@@ -38,8 +38,10 @@ struct LpArgs {
   int32_t packed;                 // packed entries allowed where the values fit
   const int32_t *aptr, *aidx;     // adjacency (positions)
   const int64_t *wv;              // [n]
-  const int32_t *hoff;            // [n + 1] first chunk of each node (chunks only for long lists)
+  const int4 *nb;                 // [n] a list of up to 4 entries (-1 past it); kLpLong in w: longer
+  const int32_t *hoff;            // [n] first chunk of a node with more than kLpLight entries
   const int32_t *hnode;           // [H] node of each chunk
+  const int32_t *hcount;          // H, the chunks of all such nodes
   int32_t *pol;                   // [n] the policy
   LpE *e0, *e1;                   // [n] each
   int64_t *hval;                  // [H] best value of each chunk
@@ -59,20 +61,53 @@ __device__ inline bool lp_better(int64_t v, int32_t q, int64_t bv, int32_t bq) {
   return v > bv || (v == bv && q < bq);
 }
 
-__global__ void k_lp_heavy_count(int32_t n, const int32_t *aptr, int32_t *hcnt, const Status *st) {
-  if (failed(st)) return;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t d = aptr[p + 1] - aptr[p];
-    hcnt[p] = d > kLpLight ? (d + kLpChunk - 1) / kLpChunk : 0;
-  }
+constexpr int32_t kLpLong = -2;
+
+// the barrier's and the counter's words, and the result's two
+__global__ void k_lp_init(int32_t *bar, int32_t nw, int32_t *res) {
+  for (int32_t i = threadIdx.x; i < nw; i += blockDim.x) bar[i] = 0;
+  if (threadIdx.x < 2) res[threadIdx.x] = 0;
 }
 
-__global__ void k_lp_heavy_fill(int32_t n, const int32_t *hoff, int32_t *hnode, const Status *st) {
+__device__ inline int32_t lp_chunks(int32_t d) { return (d + kLpChunk - 1) / kLpChunk; }
+
+// Every node's list of up to four neighbours in one 16-byte record (an
+// improvement then waits for the records and the values, not for row pointers
+// and indexes before them), and the chunks of the lists of more than kLpLight
+// entries: a node reserves its chunks by one atomic (their order is free), and
+// the whole wave writes them, since one node can have thousands.
+__global__ void k_lp_lists(int32_t n, const int32_t *aptr, const int32_t *aidx, int4 *nb,
+                           int32_t *hoff, int32_t *hnode, int32_t *hcount, const Status *st) {
   if (failed(st)) return;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x)
-    for (int32_t c = hoff[p]; c < hoff[p + 1]; c++) hnode[c] = (int32_t)p;
+  const int lane = threadIdx.x & 63;
+  for (int64_t p0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p0 - lane < n;
+       p0 += (int64_t)gridDim.x * blockDim.x) {
+    int32_t nch = 0, h = 0;
+    if (p0 < n) {
+      const int32_t e0 = aptr[p0], d = aptr[p0 + 1] - e0;
+      int4 x = make_int4(-1, -1, -1, -1);
+      if (d > 4) {
+        x.w = kLpLong;
+      } else {
+        if (d > 0) x.x = aidx[e0];
+        if (d > 1) x.y = aidx[e0 + 1];
+        if (d > 2) x.z = aidx[e0 + 2];
+        if (d > 3) x.w = aidx[e0 + 3];
+      }
+      nb[p0] = x;
+      if (d > kLpLight) {
+        nch = lp_chunks(d);
+        h = atomicAdd(hcount, nch);
+        hoff[p0] = h;
+      }
+    }
+    for (uint64_t m = __ballot(nch > 0); m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const int32_t c = __builtin_amdgcn_readlane(nch, l), hl = __builtin_amdgcn_readlane(h, l);
+      const int32_t p = __builtin_amdgcn_readlane((int32_t)p0, l);
+      for (int32_t k = lane; k < c; k += 64) hnode[hl + k] = p;
+    }
+  }
 }
 
 // KIND: 0 the b-level, 1 the t-level (out = val - wv), 2 the levels of Kahn's
@@ -89,7 +124,7 @@ __device__ inline void lp_run(const LpArgs &a, int32_t *s_okp, int32_t *s_bitp) 
   const int64_t gsz = (int64_t)gridDim.x * kLpB;
   const int64_t gid = (int64_t)blockIdx.x * kLpB + threadIdx.x;
   const int lane = threadIdx.x & 63;
-  const int32_t H = a.hoff[n];
+  const int32_t H = *a.hcount;
   int32_t bar = 0, bit;
   // the empty policy: every node alone
   for (int64_t p = gid; p < n; p += gsz) {
@@ -140,42 +175,62 @@ __device__ inline void lp_run(const LpArgs &a, int32_t *s_okp, int32_t *s_bitp) 
     int32_t chg = 0;
     // short lists, one thread per node, kLpU nodes with loads in flight
     for (int64_t p0 = gid; p0 < n; p0 += kLpU * gsz) {
-      int32_t b0[kLpU], b1[kLpU], pq[kLpU];
+      int4 q[kLpU];
+      int32_t pq[kLpU];
 #pragma unroll
       for (int u = 0; u < kLpU; u++) {
         const int64_t p = p0 + u * gsz;
-        b0[u] = b1[u] = 0;
+        q[u] = make_int4(-1, -1, -1, -1);
         pq[u] = -1;
         if (p < n) {
-          b0[u] = a.aptr[p];
-          b1[u] = a.aptr[p + 1];
+          q[u] = a.nb[p];
           pq[u] = ld32(&a.pol[p]);
         }
+      }
+      auto value = [&](int32_t x) -> int64_t {
+        return x < 0 ? -1 : (PK ? pk_val(pk_ld(E + x)) : ld_coherent(&cur[x].v));
+      };
+      int64_t v[kLpU][4];
+#pragma unroll
+      for (int u = 0; u < kLpU; u++) {
+        v[u][0] = value(q[u].x);
+        v[u][1] = value(q[u].y);
+        v[u][2] = value(q[u].z);
+        v[u][3] = value(q[u].w);
       }
 #pragma unroll
       for (int u = 0; u < kLpU; u++) {
         const int64_t p = p0 + u * gsz;
-        const int32_t d = b1[u] - b0[u];
-        if (PK && p < n && d == 0) pk_st(En + p, pk_make(a.wv[p], kPkEnd));
-        if (p >= n || d == 0 || d > kLpLight) continue;
-        int64_t bv = -1;
+        if (p >= n) continue;
+        int64_t bv = -1, cv = -1;  // the best neighbour, and the policy's (one of them)
         int32_t bq = INT32_MAX;
-        for (int32_t e0 = b0[u]; e0 < b1[u]; e0 += 4) {  // four neighbours' loads in flight
-          int32_t q[4];
-          int64_t v[4];
+        auto take = [&](int32_t x, int64_t y) {
+          if (x < 0) return;
+          if (x == pq[u]) cv = y;
+          if (lp_better(y, x, bv, bq)) {
+            bv = y;
+            bq = x;
+          }
+        };
+        if (q[u].w != kLpLong) {
+          take(q[u].x, v[u][0]);
+          take(q[u].y, v[u][1]);
+          take(q[u].z, v[u][2]);
+          take(q[u].w, v[u][3]);
+        } else {
+          const int32_t b0 = a.aptr[p], b1 = a.aptr[p + 1];
+          if (b1 - b0 > kLpLight) continue;
+          for (int32_t e0 = b0; e0 < b1; e0 += 4) {  // four neighbours' loads in flight
+            int32_t x[4];
+            int64_t y[4];
 #pragma unroll
-          for (int k = 0; k < 4; k++) q[k] = e0 + k < b1[u] ? a.aidx[e0 + k] : -1;
+            for (int k = 0; k < 4; k++) x[k] = e0 + k < b1 ? a.aidx[e0 + k] : -1;
 #pragma unroll
-          for (int k = 0; k < 4; k++)
-            v[k] = q[k] < 0 ? -1 : (PK ? pk_val(pk_ld(E + q[k])) : ld_coherent(&cur[q[k]].v));
+            for (int k = 0; k < 4; k++) y[k] = value(x[k]);
 #pragma unroll
-          for (int k = 0; k < 4; k++)
-            if (q[k] >= 0 && lp_better(v[k], q[k], bv, bq)) {
-              bv = v[k];
-              bq = q[k];
-            }
+            for (int k = 0; k < 4; k++) take(x[k], y[k]);
+          }
         }
-        const int64_t cv = pq[u] >= 0 ? (PK ? pk_val(pk_ld(E + pq[u])) : ld_coherent(&cur[pq[u]].v)) : -1;
         if (bv > cv) {
           st32(&a.pol[p], bq);
           chg = 1;
@@ -191,7 +246,8 @@ __device__ inline void lp_run(const LpArgs &a, int32_t *s_okp, int32_t *s_bitp) 
         if (c != a.hoff[p]) continue;  // uniform: the wave of the node's first chunk combines
         int64_t bv = -1;
         int32_t bq = INT32_MAX;
-        for (int32_t k = (int32_t)c + lane; k < a.hoff[p + 1]; k += 64) {
+        const int32_t ce = (int32_t)c + lp_chunks(a.aptr[p + 1] - a.aptr[p]);
+        for (int32_t k = (int32_t)c + lane; k < ce; k += 64) {
           const int64_t v = ld_coherent(&a.hval[k]);
           const int32_t q = ld32(&a.hidx[k]);
           if (lp_better(v, q, bv, bq)) {
@@ -430,23 +486,26 @@ int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
   // pointer chains are at most L nodes long (one per level)
   int32_t max_rounds = 2;
   while ((int64_t(1) << (max_rounds - 2)) < L) max_rounds++;
-  // Iterations allowed (cap <= 0: before the level sweep is cheaper): an
-  // iteration costs about max_rounds barriers and passes over 48 bytes per
-  // node, plus one pass over the neighbour lists; the sweep about 0.6 us per
-  // level after 0.5 ms.
+  // Iterations allowed (cap <= 0: before the level sweep is cheaper).  Packed
+  // entries: 37 us an iteration at 200k nodes, 147 at 1.07M.  16-byte entries:
+  // about max_rounds barriers and passes over 48 bytes per node, plus one pass
+  // over the neighbour lists.  The sweep with its preparation: 0.6 us per level
+  // and 5 ns per node (wide levels) after 0.5 ms; layered graphs of 200k nodes
+  // converge after 19 to 22 iterations, the transformer graphs after 6 to 12.
   if (cap <= 0) {
-    const double it_us = max_rounds * (5.0 + 48.0 * n / 4.0e6) + 12.0 * m / 4.0e6;
-    const double sweep_us = 500.0 + 0.6 * L;
+    const double it_us = policy_iteration_packed()
+                             ? 25.0 + 1.2e-4 * n
+                             : max_rounds * (5.0 + 48.0 * n / 4.0e6) + 12.0 * m / 4.0e6;
+    const double sweep_us = 500.0 + 0.6 * L + (policy_iteration_packed() ? 5e-3 * n : 0.0);
     cap = (int32_t)(sweep_us / it_us);
     if (cap < 2) cap = 2;
   }
-  int32_t *hcnt, *hoff, *hnode, *pol, *hidx, *bar;
+  int32_t *hoff, *hnode, *pol, *hidx, *bar;
   LpE *e0, *e1;
   int64_t *hval;
-  CEL_TRY(sc.get(&hcnt, n));
-  CEL_TRY(sc.get(&hoff, (int64_t)n + 1));
-  k_lp_heavy_count<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, aptr, hcnt, st);
-  CEL_TRY(exclusive_scan_i32(hcnt, hoff, n, sc, s));
+  int4 *nb;
+  CEL_TRY(sc.get(&hoff, n));
+  CEL_TRY(sc.get(&nb, n));
   // chunks: at most m / kLpChunk + (nodes with long lists) <= m / kLpChunk + m / kLpLight
   const int64_t hmax = (int64_t)m / kLpChunk + (int64_t)m / kLpLight + 1;
   CEL_TRY(sc.get(&hnode, hmax));
@@ -455,10 +514,9 @@ int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
   CEL_TRY(sc.get(&pol, n));
   CEL_TRY(sc.get(&e0, n));
   CEL_TRY(sc.get(&e1, n));
-  CEL_TRY(sc.get(&bar, 2 + (int64_t)G));
-  k_lp_heavy_fill<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, hoff, hnode, st);
-  k_fill_i32<<<1, 256, 0, s>>>(bar, 2 + (int64_t)G, 0);
-  k_fill_i32<<<1, 64, 0, s>>>(res, 2, 0);
+  CEL_TRY(sc.get(&bar, 3 + (int64_t)G));  // the barrier's words, then the chunk counter
+  k_lp_init<<<1, 256, 0, s>>>(bar, 3 + G, res);
+  k_lp_lists<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, aptr, aidx, nb, hoff, hnode, bar + 2 + G, st);
   CEL_HIP(hipGetLastError());
   LpArgs a{};
   a.n = n;
@@ -468,7 +526,9 @@ int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
   a.aptr = aptr;
   a.aidx = aidx;
   a.wv = wv;
+  a.nb = nb;
   a.hoff = hoff;
+  a.hcount = bar + 2 + G;
   a.hnode = hnode;
   a.pol = pol;
   a.e0 = e0;
