@@ -121,14 +121,12 @@ extern "C" int cel_blevel(const cel_graph *g, const cel_devices *d, const int32_
   if (flags & ~CEL_COMM_OFF) return set_error(CEL_E_ARG, "%s: unknown flags", fn);
   Scratch sc(s);
   Status *st;
-  int32_t *tmp, *pos, *sptr, *sidx;
+  int32_t *pos, *sptr, *sidx;
   int64_t *wp, *wcp, *blp;
   CEL_TRY(sc.get(&st, 1));
-  CEL_TRY(sc.get(&tmp, n));
   CEL_TRY(sc.get(&pos, n));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
-  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, tmp, sc, s));
-  CEL_TRY(check_level_order(g, order_id, level, level_ptr, L, pos, st, s));
+  CEL_TRY(check_graph_levels(g, d->bw, d->lat, order_id, level, level_ptr, L, pos, st, sc, s));
   CEL_TRY(sc.get(&sptr, (int64_t)n + 1));
   CEL_TRY(sc.get(&sidx, g->m));
   CEL_TRY(sc.get(&wp, n));

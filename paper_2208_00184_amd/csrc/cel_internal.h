@@ -22,10 +22,10 @@ enum : uint32_t { EB_ARG = 1u, EB_CYCLE = 2u, EB_OVERFLOW = 4u, EB_ORDER = 8u, E
 // return without touching data addressed by unchecked indices.
 struct Status {
   uint32_t err;
-  uint32_t pad;
+  uint32_t done;       // groups of blocks of k_check_edges that ended
   uint64_t total;      // saturating sum(w) + sum over edges c[src]
   int64_t s0, s1, s2;  // call-specific scalar results
-  int32_t i0, i1, i2, i3;
+  int32_t i0, i1, i2, i3, i4, pad;
 };
 
 __host__ __device__ inline int64_t comm_of(int64_t ob, int64_t bw, int64_t lat) {
@@ -180,17 +180,22 @@ __device__ inline int64_t heavy_max(int32_t e0, int32_t e1, int tid, IndexF inde
   return mx;
 }
 
-// Edge-balanced CSR traversal: block b takes edges [b * kEdgesPB, +kEdgesPB)
+// Edge-balanced CSR traversal: block b takes edges [b * edges_pb, +edges_pb)
 // whatever their sources, so a node of huge out-degree is spread over many
 // blocks.  Wave 0 finds the rows of the slice's first and last edge by a
 // 64-way search over out_ptr; the slice's row pointers are staged in LDS
 // (kRowsPB at most, else the per-edge search reads out_ptr).  Row pointers must
 // already be validated (non-decreasing, out_ptr[0] = 0, out_ptr[n] = m).
-constexpr int kEdgesPB = 2048;
+// A slice is 2048 edges, eight for each thread, which pays for the search of
+// its rows; up to 512 Ki edges it is 256, one for each thread, so that a small
+// graph's edges do not sit in a handful of workgroups (8,000 edges, 4 of them:
+// 13 to 21 us a kernel; 32: 5 to 6).
 constexpr int kRowsPB = 1024;
 
+__host__ __device__ inline int edges_pb(int32_t m) { return m <= (1 << 19) ? 256 : 2048; }
+
 inline unsigned edge_blocks(int32_t m) {
-  return m > 0 ? (unsigned)((m + kEdgesPB - 1) / kEdgesPB) : 1u;
+  return m > 0 ? (unsigned)(((int64_t)m + edges_pb(m) - 1) / edges_pb(m)) : 1u;
 }
 
 // last u in [0, n) with out_ptr[u] <= x, for 0 <= x < m; wave-uniform result
@@ -212,14 +217,15 @@ __device__ inline int32_t wave_row_of(const int32_t *out_ptr, int32_t n, int32_t
   return lo;
 }
 
-// Calls f(u, e) for every edge e of the block's slice, u its source.  s_ptr
-// holds kRowsPB + 1 ints, s_u two.
+// Calls f(u, e) for every edge e of slice `slice`, u its source.  s_ptr holds
+// kRowsPB + 1 ints, s_u two.
 template <class F>
-__device__ inline void for_edges_balanced(const int32_t *out_ptr, int32_t n, int32_t m,
-                                          int32_t *s_ptr, int32_t *s_u, F f) {
-  const int64_t e0 = (int64_t)blockIdx.x * kEdgesPB;
+__device__ inline void for_edges_slice(unsigned slice, const int32_t *out_ptr, int32_t n, int32_t m,
+                                       int32_t *s_ptr, int32_t *s_u, F f) {
+  const int epb = edges_pb(m);
+  const int64_t e0 = (int64_t)slice * epb;
   if (e0 >= m) return;  // uniform over the block
-  const int32_t e1 = e0 + kEdgesPB < m ? (int32_t)(e0 + kEdgesPB) : m;
+  const int32_t e1 = e0 + epb < m ? (int32_t)(e0 + epb) : m;
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     const int32_t u0 = wave_row_of(out_ptr, n, (int32_t)e0, lane);
@@ -244,6 +250,13 @@ __device__ inline void for_edges_balanced(const int32_t *out_ptr, int32_t n, int
     }
     f(u0 + lo, e);
   }
+}
+
+// The same for the slice of the block's own index.
+template <class F>
+__device__ inline void for_edges_balanced(const int32_t *out_ptr, int32_t n, int32_t m,
+                                          int32_t *s_ptr, int32_t *s_u, F f) {
+  for_edges_slice(blockIdx.x, out_ptr, n, m, s_ptr, s_u, f);
 }
 
 // Phase timers for tuning builds (-DCEL_PHASE_TIMERS): thread 0 of each
@@ -364,23 +377,27 @@ int check_host_devices(const cel_devices *d, const char *fn);
 // edge multiset (compared by a hash total of the (source, target) pairs).
 // Fills indeg_scratch (n ints) with the in-degrees.  Raises EB_ARG /
 // EB_OVERFLOW in st.
-int check_graph(const cel_graph *g, int64_t bw, int64_t lat, bool bound, Status *st,
-                int32_t *indeg_scratch, Scratch &sc, hipStream_t s);
+int check_graph(const cel_graph *g, int64_t bw, int64_t lat, bool bound, Status *st, Scratch &sc,
+                hipStream_t s);
 
-// Checks that `order` is a permutation of 0..n-1 consistent with level /
-// level_ptr (level-monotone) and that level[u] < level[v] on every edge.
-// Fills pos (inverse permutation).  Raises EB_ORDER.
-int check_level_order(const cel_graph *g, const int32_t *order, const int32_t *level,
-                      const int32_t *level_ptr, int32_t L, int32_t *pos, Status *st,
-                      hipStream_t s);
+// The same (with the bound), and that `order` is a permutation of 0..n-1
+// consistent with level / level_ptr (level-monotone) and that level[u] <
+// level[v] on every edge.  Fills pos (inverse permutation).  Raises EB_ORDER.
+int check_graph_levels(const cel_graph *g, int64_t bw, int64_t lat, const int32_t *order,
+                       const int32_t *level, const int32_t *level_ptr, int32_t L, int32_t *pos,
+                       Status *st, Scratch &sc, hipStream_t s);
 
-// Checks that `order` is a permutation with pos[u] < pos[v] on every edge.
-int check_topo_order(const cel_graph *g, const int32_t *order, int32_t *pos, Status *st,
-                     hipStream_t s);
+// check_graph, and that `order` is a permutation with pos[u] < pos[v] on every
+// edge.
+int check_graph_topo(const cel_graph *g, int64_t bw, int64_t lat, bool bound, const int32_t *order,
+                     int32_t *pos, Status *st, Scratch &sc, hipStream_t s);
 
-// out[0] = 0, out[i+1] = out[i] + in[i] for i < n (n+1 outputs).
-int exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Scratch &sc, hipStream_t s);
-int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, Scratch &sc, hipStream_t s);
+// out[0] = 0, out[i+1] = out[i] + in[i] for i < n (n+1 outputs); total (device
+// memory, may be null) takes out[n] too.
+int exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Scratch &sc, hipStream_t s,
+                       int32_t *total = nullptr);
+int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, Scratch &sc, hipStream_t s,
+                       int64_t *total = nullptr);
 
 // Relabels a CSR (ptr/idx over node ids, m edges, validated) into position
 // space of `order`: row p lists pos[idx[k]] for the edges of node order[p].

@@ -231,9 +231,9 @@ __device__ inline int32_t first_le(const int32_t *q, int32_t cnt, int32_t thr, i
 
 // Per block of 64 targets (block b: j in [64b, 64b + 64)): the number of
 // in-edges of positions [64b, min(64b + 64, n)) whose source is at or after
-// lo(64b), and the largest such count.  One wave per block.
+// lo(64b).  One wave per block.
 __global__ void k_dp_count(int32_t n, int32_t nb, const int32_t *pptr, const int32_t *pidx,
-                           const int32_t *lo, int32_t *cnt, int32_t *mx, const Status *st) {
+                           const int32_t *lo, int32_t *cnt, const Status *st) {
   if (failed(st)) return;
   const int lane = threadIdx.x & 63;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -244,10 +244,7 @@ __global__ void k_dp_count(int32_t n, int32_t nb, const int32_t *pptr, const int
     int32_t c = 0;
     for (int32_t e = pptr[j0] + lane; e < e1; e += 64) c += pidx[e] >= lo0;
     for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-    if (lane == 0) {
-      cnt[b] = c;
-      atomicMax(mx, c);
-    }
+    if (lane == 0) cnt[b] = c;
   }
 }
 
@@ -1083,20 +1080,14 @@ static int dp_blocked(int32_t n, int32_t m, int32_t R, const int32_t *lo, const 
                       Status *st, Scratch &sc, hipStream_t s, bool *done) {
   *done = false;
   const int32_t nb = n / 64 + 1;
-  int32_t *bcnt, *boff, *mx;
+  int32_t *bcnt, *boff;
   CEL_TRY(sc.get(&bcnt, nb));
   CEL_TRY(sc.get(&boff, (int64_t)nb + 1));
-  CEL_TRY(sc.get(&mx, 1));
-  CEL_HIP(hipMemsetAsync(mx, 0, sizeof(int32_t), s));
-  {
-    k_dp_count<<<grid_for((int64_t)nb * 64, 256, 4096), 256, 0, s>>>(n, nb, pptr, pidx, lo, bcnt,
-                                                                     mx, st);
-  }
+  k_dp_count<<<grid_for((int64_t)nb * 64, 256, 4096), 256, 0, s>>>(n, nb, pptr, pidx, lo, bcnt, st);
   CEL_TRY(exclusive_scan_i32(bcnt, boff, nb, sc, s));
-  int64_t total = 0;
-  CEL_HIP(hipMemcpyAsync(&total, PO + n, sizeof total, hipMemcpyDeviceToHost, s));
-  CEL_HIP(hipStreamSynchronize(s));
-  if (total >= kPackLim) return CEL_OK;  // step-wise kernel (keys need values below 2^48)
+  Status h;
+  CEL_TRY(read_status(st, &h, s));
+  if (h.s1 >= kPackLim) return CEL_OK;  // step-wise kernel (keys need values below 2^48)
   int32_t *eq, *et;
   int64_t *ec, *eE;
   CEL_TRY(sc.get(&eq, m));
@@ -1167,13 +1158,11 @@ extern "C" int cel_cluster(const cel_graph *g, const cel_devices *d, const int32
   }
   Scratch sc(s);
   Status *st;
-  int32_t *tmp, *pos;
+  int32_t *pos;
   CEL_TRY(sc.get(&st, 1));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
-  CEL_TRY(sc.get(&tmp, n));
   CEL_TRY(sc.get(&pos, n));
-  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, tmp, sc, s));
-  CEL_TRY(check_topo_order(g, order, pos, st, s));
+  CEL_TRY(check_graph_topo(g, d->bw, d->lat, true, order, pos, st, sc, s));
   if (n == 0) {
     Status h;
     CEL_TRY(read_status(st, &h, s));
@@ -1203,7 +1192,7 @@ extern "C" int cel_cluster(const cel_graph *g, const cel_devices *d, const int32
     CEL_TRY(sc.get(&pptr, (int64_t)n + 1));
     CEL_TRY(sc.get(&pidx, g->m));
     CEL_TRY(sc.get(&P, (int64_t)n + 1));
-    CEL_TRY(exclusive_scan_i64(outc, PO, n, sc, s));
+    CEL_TRY(exclusive_scan_i64(outc, PO, n, sc, s, &st->s1));  // s1: the comm of all edges
     // policy iteration first (graphs of kDpPolicyN nodes and more)
     bool solved = false;
     t_cl_info = {1, 0};

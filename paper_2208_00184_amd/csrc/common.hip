@@ -211,13 +211,57 @@ __device__ inline uint64_t sat_add(uint64_t a, uint64_t b) {
   return (r < a || r > (uint64_t)kLim) ? (uint64_t)kLim : r;
 }
 
-__global__ void k_check_nodes(cel_graph g, int64_t bw, int64_t lat, Status *st, uint64_t *part_out) {
+// What a call's order array is checked against.
+enum OrderKind { kNoOrder = 0, kLevelOrder = 1, kTopoOrder = 2 };
+struct OrderCheck {
+  const int32_t *order, *level, *level_ptr;
+  int32_t L;
+  int32_t *pos;
+};
+
+constexpr uint32_t kCheckGroups = 64;  // at most the block size
+constexpr uint32_t kCheckStride = 32;  // counters 128 bytes apart
+
+// Every call opens with these checks, and on a graph of a few thousand nodes
+// a launch costs more than the work in it: two launches hold all of them
+// (they were five for the graph and four more for an order).  Here: what
+// reads one node or one position; k_check_edges: what follows edges or needs
+// the inverse order.
+//
+// Node fields and row pointers; the block's part of the overflow bound; with
+// an order, its ids in range, pos[order[p]] = p, and (level orders) level_ptr
+// and the place of every node's level in it.  Clears k_check_edges' counters.
+template <int KIND>
+__global__ void k_check_nodes(cel_graph g, int64_t bw, int64_t lat, OrderCheck oc, Status *st,
+                              uint64_t *part_out, uint32_t *groups) {
   __shared__ uint64_t part[4];
+  if (blockIdx.x == 0 && threadIdx.x < kCheckGroups) groups[threadIdx.x * kCheckStride] = 0;
   const int32_t n = g.n, m = g.m;
   uint64_t acc = 0;
   uint32_t bad = 0;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v <= n;
        v += (int64_t)gridDim.x * blockDim.x) {
+    if (KIND == kLevelOrder && v <= oc.L) {  // 0 at the front, n at the back, non-decreasing
+      const int32_t a = oc.level_ptr[v];
+      if (v == 0 && a != 0) bad |= EB_ORDER;
+      if (v == oc.L && a != n) bad |= EB_ORDER;
+      if (v < oc.L && oc.level_ptr[v + 1] < a) bad |= EB_ORDER;
+    }
+    if (KIND != kNoOrder && v < n) {
+      const int32_t u = oc.order[v];
+      if (u < 0 || u >= n) {
+        bad |= EB_ORDER;
+      } else {
+        // duplicates are found by k_check_edges: two positions naming one id
+        // leave pos[id] at one of them, and the other does not read itself back
+        oc.pos[u] = (int32_t)v;
+        if (KIND == kLevelOrder) {
+          const int32_t l = oc.level[u];
+          if (l < 0 || l >= oc.L || v < oc.level_ptr[l] || v >= oc.level_ptr[l + 1])
+            bad |= EB_ORDER;
+        }
+      }
+    }
     if (v == 0 && (g.out_ptr[0] != 0 || g.in_ptr[0] != 0)) bad |= EB_ARG;
     if (v == n) {
       if (g.out_ptr[n] != m || g.in_ptr[n] != m) bad |= EB_ARG;
@@ -259,255 +303,162 @@ __device__ inline uint64_t mix64(uint64_t x) {  // SplitMix64 finaliser
   return x ^ (x >> 31);
 }
 
-// CSR and CSC must hold the same edge multiset.  Each side adds a 64-bit hash
-// of every (source, target) pair into one total (block sums, one atomic per
-// block); equal multisets give equal totals, and any difference is caught with
-// overwhelming probability.  The CSC pass also writes each node's in-degree.
+// CSR and CSC must hold the same edge multiset.  The CSR side adds a 64-bit
+// hash of every (source, target) pair to one total and the CSC side takes it
+// away; equal multisets leave 0, and any difference is caught with
+// overwhelming probability.
 __device__ inline uint64_t pair_hash(int32_t u, int32_t v) {
   return mix64(((uint64_t)(uint32_t)u << 32) | (uint32_t)v);
 }
 
-// failed(st) read once per block, so that every thread of the block returns
-// or none does (the kernels below reach block-wide barriers)
-__device__ inline bool block_failed(const Status *st, int *flag) {
-  if (threadIdx.x == 0) *flag = failed(st) ? 1 : 0;
-  __syncthreads();
-  return *flag != 0;
-}
-
-// the block's sum of x into *dst (one plain store per block: blocks write
-// their own partials, which one small kernel adds up, so no address takes
-// thousands of atomics)
-__device__ inline void block_sum_u64(unsigned long long *dst, uint64_t x, uint64_t *red) {
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t t = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); i++) t += red[i];
-    *dst = (unsigned long long)t;
-  }
-}
-
-// CSR pass over edge-balanced blocks: target ranges and the pair-hash total
-// (hs[block]: the block's part).
-__global__ void k_check_csr(cel_graph g, Status *st, unsigned long long *hs) {
+// After k_check_nodes.  Blocks [0, eb) take the out-edges (targets in range,
+// pair hashes, source before target in the order), blocks [eb, 2 eb) the
+// in-edges (sources in range, pair hashes), both edge-balanced; every block
+// takes its share of the positions (pos[order[p]] = p: a permutation).  The
+// last block to end compares the hash totals and, if asked, adds up the
+// overflow bound.  Row pointers that failed leave the edges out, order ids
+// out of range the positions; levels that failed are compared all the same
+// (the call is refused already, and an argument error is reported before an
+// order error whatever the checks after it find).
+//
+// Blocks store their part of the hash and count themselves in one of
+// kCheckGroups counters, the last of a group in st->done.  The counting is
+// relaxed, after a wait for the block's own store, and the last block reads
+// the parts past the caches: a release in each of 3,200 blocks would write
+// back an L2 each time (65 us for a kernel of 10), and that many adds to one
+// address are no faster.
+template <int KIND>
+__global__ void __launch_bounds__(256) k_check_edges(cel_graph g, OrderCheck oc, int eb, int bound,
+                                                     const uint64_t *part, int np, uint64_t *hs,
+                                                     uint32_t *groups, Status *st) {
   __shared__ int32_t ptr[kRowsPB + 1], su[2];
-  __shared__ uint64_t red[16];
-  __shared__ int s_f;
-  if (block_failed(st, &s_f)) return;  // row pointers not validated
+  __shared__ uint64_t red[4], redh[4];
+  __shared__ uint32_t s_err;
+  __shared__ int s_last;
   const int32_t n = g.n;
-  uint32_t bad = 0;
-  uint64_t acc = 0;
-  for_edges_balanced(g.out_ptr, n, g.m, ptr, su, [&](int32_t u, int32_t e) {
-    const int32_t t = g.out_idx[e];
-    if (t < 0 || t >= n) {
-      bad |= EB_ARG;
-      return;
-    }
-    acc += pair_hash(u, t);
-  });
-  if (bad) raise_err(st, bad);
-  block_sum_u64(&hs[blockIdx.x], acc, red);
-}
-
-// CSC pass: source ranges, in-degrees and the pair-hash total (hs[block]).
-__global__ void k_check_csc(cel_graph g, Status *st, int32_t *indeg, unsigned long long *hs) {
-  __shared__ uint64_t red[16];
-  __shared__ int s_f;
-  if (block_failed(st, &s_f)) return;
-  uint32_t bad = 0;
-  uint64_t acc = 0;
-  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < g.n;
-       v += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t k0 = g.in_ptr[v], k1 = g.in_ptr[v + 1];
-    indeg[v] = k1 - k0;
-    for (int32_t k = k0; k < k1; k++) {
-      const int32_t s = g.in_idx[k];
-      if (s < 0 || s >= g.n) {
-        bad |= EB_ARG;
-        break;
-      }
-      acc += pair_hash(s, (int32_t)v);
-    }
-  }
-  if (bad) raise_err(st, bad);
-  block_sum_u64(&hs[blockIdx.x], acc, red);
-}
-
-// the two totals from the blocks' parts: [0, na) for the CSR side, then nb
-// for the CSC side (a failed earlier check leaves parts unwritten: skipped)
-__global__ void k_check_pairs(const unsigned long long *hs, int na, int nb, Status *st) {
-  __shared__ uint64_t red[2][4];
-  if (failed(st)) return;
-  uint64_t a = 0, b = 0;
-  for (int i = threadIdx.x; i < na; i += blockDim.x) a += hs[i];
-  for (int i = threadIdx.x; i < nb; i += blockDim.x) b += hs[na + i];
-  for (int off = 32; off > 0; off >>= 1) {
-    a += __shfl_down(a, off);
-    b += __shfl_down(b, off);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = a;
-    red[1][threadIdx.x >> 6] = b;
-  }
+  if (threadIdx.x == 0) s_err = __atomic_load_n(&st->err, __ATOMIC_RELAXED);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t ta = 0, tb = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); i++) {
-      ta += red[0][i];
-      tb += red[1][i];
-    }
-    if (ta != tb) raise_err(st, EB_ARG);
-  }
-}
-
-// one block: saturating sum of the per-block partials
-__global__ void k_finish_overflow(const uint64_t *part, int np, Status *st) {
-  __shared__ uint64_t red[4];
+  const uint32_t err = s_err;
+  uint32_t bad = 0;
   uint64_t acc = 0;
-  for (int i = threadIdx.x; i < np; i += blockDim.x) acc = sat_add(acc, part[i]);
-  for (int off = 32; off > 0; off >>= 1) acc = sat_add(acc, __shfl_down(acc, off));
+  if (!(err & EB_ARG) && n > 0) {
+    const bool out = (int)blockIdx.x < eb;
+    if (out) {
+      for_edges_slice(blockIdx.x, g.out_ptr, n, g.m, ptr, su, [&](int32_t u, int32_t e) {
+        const int32_t t = g.out_idx[e];
+        if (t < 0 || t >= n) {
+          bad |= EB_ARG;
+          return;
+        }
+        if (KIND == kLevelOrder && oc.level[t] <= oc.level[u]) bad |= EB_ORDER;
+        if (KIND == kTopoOrder && oc.pos[t] <= oc.pos[u]) bad |= EB_ORDER;
+        acc += pair_hash(u, t);
+      });
+    } else if ((int)blockIdx.x < 2 * eb) {
+      for_edges_slice(blockIdx.x - eb, g.in_ptr, n, g.m, ptr, su, [&](int32_t v, int32_t k) {
+        const int32_t u = g.in_idx[k];
+        if (u < 0 || u >= n) {
+          bad |= EB_ARG;
+          return;
+        }
+        acc -= pair_hash(u, v);
+      });
+    }
+  }
+  if (KIND != kNoOrder && !(err & EB_ORDER))
+    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
+         p += (int64_t)gridDim.x * blockDim.x)
+      if (oc.pos[oc.order[p]] != (int32_t)p) bad |= EB_ORDER;
+  if (bad) raise_err(st, bad);
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint64_t t = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); i++) t = sat_add(t, red[i]);
-    st->total = t;
-    if (t >= (uint64_t)kLim) raise_err(st, EB_OVERFLOW);
+    __hip_atomic_store(&hs[blockIdx.x], red[0] + red[1] + red[2] + red[3], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the store is complete
+    const uint32_t k = blockIdx.x % kCheckGroups;
+    const uint32_t size = (gridDim.x - k + kCheckGroups - 1) / kCheckGroups;
+    bool last = __hip_atomic_fetch_add(&groups[k * kCheckStride], 1u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT) == size - 1;
+    if (last)
+      last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+             (gridDim.x < kCheckGroups ? gridDim.x : kCheckGroups) - 1;
+    s_last = last;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  uint64_t tot = 0, hash = 0;
+  for (int i = threadIdx.x; i < (int)gridDim.x; i += blockDim.x)
+    hash += __hip_atomic_load(&hs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (bound)
+    for (int i = threadIdx.x; i < np; i += blockDim.x) tot = sat_add(tot, part[i]);
+  for (int off = 32; off > 0; off >>= 1) {
+    tot = sat_add(tot, __shfl_down(tot, off));
+    hash += __shfl_down(hash, off);
+  }
+  if ((threadIdx.x & 63) == 0) {  // red was read before the barrier
+    red[threadIdx.x >> 6] = tot;
+    redh[threadIdx.x >> 6] = hash;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (redh[0] + redh[1] + redh[2] + redh[3] != 0) raise_err(st, EB_ARG);
+    if (bound) {
+      uint64_t t = 0;
+      for (int i = 0; i < 4; i++) t = sat_add(t, red[i]);
+      st->total = t;
+      if (t >= (uint64_t)kLim) raise_err(st, EB_OVERFLOW);
+    }
   }
 }
 
-int check_graph(const cel_graph *g, int64_t bw, int64_t lat, bool bound, Status *st,
-                int32_t *indeg, Scratch &sc, hipStream_t s) {
+template <int KIND>
+static int check_all(const cel_graph *g, int64_t bw, int64_t lat, bool bound, const OrderCheck &oc,
+                     Status *st, Scratch &sc, hipStream_t s) {
   const int B = 256;
   const int nbk = grid_for((int64_t)g->n + 1, B, 2048);
   uint64_t *part;
+  uint32_t *groups;
   CEL_TRY(sc.get(&part, nbk));
-  k_check_nodes<<<nbk, B, 0, s>>>(*g, bw, lat, st, part);
-  if (g->n > 0) {
-    const int na = (int)edge_blocks(g->m), nc = grid_for(g->n, B, 4096);
-    unsigned long long *hs;
-    CEL_TRY(sc.get(&hs, (int64_t)na + nc));
-    k_check_csr<<<na, B, 0, s>>>(*g, st, hs);
-    k_check_csc<<<nc, B, 0, s>>>(*g, st, indeg, hs + na);
-    k_check_pairs<<<1, B, 0, s>>>(hs, na, nc, st);
+  CEL_TRY(sc.get(&groups, kCheckGroups * kCheckStride));
+  k_check_nodes<KIND><<<nbk, B, 0, s>>>(*g, bw, lat, oc, st, part, groups);
+  const int eb = (int)edge_blocks(g->m);
+  int grid = 2 * eb;
+  if (KIND != kNoOrder) {  // few edges and many positions: blocks for the positions alone
+    const int pb = grid_for(g->n, B, 512);
+    if (grid < pb) grid = pb;
   }
-  if (bound) k_finish_overflow<<<1, B, 0, s>>>(part, nbk, st);
+  uint64_t *hs;
+  CEL_TRY(sc.get(&hs, grid));
+  k_check_edges<KIND><<<grid, B, 0, s>>>(*g, oc, eb, bound ? 1 : 0, part, nbk, hs, groups,
+                                         st);
   CEL_HIP(hipGetLastError());
   return CEL_OK;
+}
+
+int check_graph(const cel_graph *g, int64_t bw, int64_t lat, bool bound, Status *st, Scratch &sc,
+                hipStream_t s) {
+  return check_all<kNoOrder>(g, bw, lat, bound, OrderCheck{}, st, sc, s);
+}
+
+int check_graph_levels(const cel_graph *g, int64_t bw, int64_t lat, const int32_t *order,
+                       const int32_t *level, const int32_t *level_ptr, int32_t L, int32_t *pos,
+                       Status *st, Scratch &sc, hipStream_t s) {
+  return check_all<kLevelOrder>(g, bw, lat, true, OrderCheck{order, level, level_ptr, L, pos}, st,
+                                sc, s);
+}
+
+int check_graph_topo(const cel_graph *g, int64_t bw, int64_t lat, bool bound, const int32_t *order,
+                     int32_t *pos, Status *st, Scratch &sc, hipStream_t s) {
+  return check_all<kTopoOrder>(g, bw, lat, bound, OrderCheck{order, nullptr, nullptr, 0, pos}, st,
+                               sc, s);
 }
 
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
-}
-
-// pos[order[p]] = p; out-of-range ids raise EB_ORDER.  Duplicates are found
-// by k_perm_verify: two positions naming one id leave pos[id] at one of them,
-// and the other no longer reads itself back.
-__global__ void k_inverse_perm(int32_t n, const int32_t *order, int32_t *pos, Status *st) {
-  uint32_t bad = 0;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    int32_t v = order[p];
-    if (v < 0 || v >= n) {
-      bad |= EB_ORDER;
-      continue;
-    }
-    pos[v] = (int32_t)p;
-  }
-  if (bad) raise_err(st, bad);
-}
-
-__global__ void k_perm_verify(int32_t n, const int32_t *order, const int32_t *pos, Status *st) {
-  if (failed(st)) return;  // ids not in range
-  uint32_t bad = 0;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x)
-    if (pos[order[p]] != (int32_t)p) bad |= EB_ORDER;
-  if (bad) raise_err(st, bad);
-}
-
-__global__ void k_check_levels_nodes(int32_t n, const int32_t *order, const int32_t *level,
-                                     const int32_t *lp, int32_t L, Status *st) {
-  uint32_t bad = 0;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p <= n;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    if (p <= L) {  // level_ptr: 0 at the front, n at the back, non-decreasing
-      int32_t a = lp[p];
-      if (p == 0 && a != 0) bad |= EB_ORDER;
-      if (p == L && a != n) bad |= EB_ORDER;
-      if (p < L && lp[p + 1] < a) bad |= EB_ORDER;
-    }
-    if (p == n) continue;
-    int32_t v = order[p];
-    if (v < 0 || v >= n) {
-      bad |= EB_ORDER;
-      continue;
-    }
-    int32_t l = level[v];
-    if (l < 0 || l >= L) {
-      bad |= EB_ORDER;
-      continue;
-    }
-    if (p < lp[l] || p >= lp[l + 1]) bad |= EB_ORDER;
-  }
-  if (bad) raise_err(st, bad);
-}
-
-// level[u] < level[v] on every edge (needs level values in range: checked above)
-__global__ void k_check_levels_edges(cel_graph g, const int32_t *level, int32_t L, Status *st) {
-  __shared__ int32_t ptr[kRowsPB + 1], su[2];
-  if (failed(st)) return;  // edge indices or level values not validated
-  uint32_t bad = 0;
-  for_edges_balanced(g.out_ptr, g.n, g.m, ptr, su, [&](int32_t u, int32_t e) {
-    if (level[g.out_idx[e]] <= level[u]) bad |= EB_ORDER;
-  });
-  if (bad) raise_err(st, bad);
-}
-
-// pos[u] < pos[v] on every edge (pos must be a complete permutation: checked)
-__global__ void k_check_topo_edges(cel_graph g, const int32_t *pos, Status *st) {
-  __shared__ int32_t ptr[kRowsPB + 1], su[2];
-  if (failed(st)) return;
-  uint32_t bad = 0;
-  for_edges_balanced(g.out_ptr, g.n, g.m, ptr, su, [&](int32_t u, int32_t e) {
-    if (pos[g.out_idx[e]] <= pos[u]) bad |= EB_ORDER;
-  });
-  if (bad) raise_err(st, bad);
-}
-
-int check_level_order(const cel_graph *g, const int32_t *order, const int32_t *level,
-                      const int32_t *level_ptr, int32_t L, int32_t *pos, Status *st,
-                      hipStream_t s) {
-  const int B = 256;
-  const int32_t n = g->n;
-  if (n > 0) {
-    k_fill_i32<<<grid_for(n, B, 4096), B, 0, s>>>(pos, n, -1);
-    k_inverse_perm<<<grid_for(n, B, 4096), B, 0, s>>>(n, order, pos, st);
-    k_perm_verify<<<grid_for(n, B, 4096), B, 0, s>>>(n, order, pos, st);
-  }
-  k_check_levels_nodes<<<grid_for((int64_t)n + 1, B, 4096), B, 0, s>>>(n, order, level, level_ptr,
-                                                                       L, st);
-  if (n > 0) k_check_levels_edges<<<edge_blocks(g->m), B, 0, s>>>(*g, level, L, st);
-  CEL_HIP(hipGetLastError());
-  return CEL_OK;
-}
-
-int check_topo_order(const cel_graph *g, const int32_t *order, int32_t *pos, Status *st,
-                     hipStream_t s) {
-  const int B = 256;
-  const int32_t n = g->n;
-  if (n > 0) {
-    k_fill_i32<<<grid_for(n, B, 4096), B, 0, s>>>(pos, n, -1);
-    k_inverse_perm<<<grid_for(n, B, 4096), B, 0, s>>>(n, order, pos, st);
-    k_perm_verify<<<grid_for(n, B, 4096), B, 0, s>>>(n, order, pos, st);
-    k_check_topo_edges<<<edge_blocks(g->m), B, 0, s>>>(*g, pos, st);
-  }
-  CEL_HIP(hipGetLastError());
-  return CEL_OK;
 }
 
 // ------------------------------------------------------------------- scans
@@ -535,34 +486,67 @@ __device__ T block_exclusive_scan(T x, T *wsum, T *total) {
   return base + inc - x;
 }
 
+// What is summed: an array, or the row lengths of a CSR taken in the order of
+// `order` (0 after a failed check, whose ids may be out of range).
 template <class T>
-__global__ void k_scan_reduce(const T *in, int64_t n, T *bsum) {
+struct ScanArray {
+  const T *in;
+  __device__ void open() {}
+  __device__ T operator()(int64_t i) const { return in[i]; }
+};
+struct ScanRows {
+  const int32_t *order, *ptr;
+  const Status *st;
+  bool ok;
+  __device__ void open() { ok = !failed(st); }
+  __device__ int32_t operator()(int64_t i) const {
+    if (!ok) return 0;
+    const int32_t v = order[i];
+    return ptr[v + 1] - ptr[v];
+  }
+};
+
+// A scan is one launch up to a tile of kScanTile values and two above: the
+// blocks' sums, then the scan, in which every block adds up the sums before
+// its own (up to kScanFlat of them; more are scanned first).
+template <class T, class F>
+__global__ void k_scan_reduce(F f, int64_t n, T *bsum) {
   __shared__ T wsum[kScanB / 64];
   int64_t base = (int64_t)blockIdx.x * kScanTile;
   T acc = 0;
+  f.open();
   for (int i = threadIdx.x; i < kScanTile; i += kScanB) {
     int64_t k = base + i;
-    if (k < n) acc += in[k];
+    if (k < n) acc += f(k);
   }
   T tot;
   (void)block_exclusive_scan<T>(acc, wsum, &tot);
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-template <class T>
-__global__ void k_scan_apply(const T *in, T *out, int64_t n, const T *boff) {
+// boff: the offset of every block; else bsum, the sums of the blocks (or one
+// block, both null).  total, if given, takes the sum of all.
+template <class T, class F>
+__global__ void k_scan_apply(F f, T *out, int64_t n, const T *bsum, const T *boff, T *total) {
   __shared__ T buf[kScanTile];
   __shared__ T wsum[kScanB / 64];
   int64_t base = (int64_t)blockIdx.x * kScanTile;
+  f.open();
   for (int i = threadIdx.x; i < kScanTile; i += kScanB) {
     int64_t k = base + i;
-    buf[i] = k < n ? in[k] : (T)0;
+    buf[i] = k < n ? f(k) : (T)0;
+  }
+  T pre = boff ? boff[blockIdx.x] : (T)0;
+  if (bsum) {  // uniform
+    T a = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanB) a += bsum[i];
+    (void)block_exclusive_scan<T>(a, wsum, &pre);
   }
   __syncthreads();
   T loc = 0;
   for (int k = 0; k < kScanItems; k++) loc += buf[threadIdx.x * kScanItems + k];
   T tot;
-  T run = block_exclusive_scan<T>(loc, wsum, &tot) + (boff ? boff[blockIdx.x] : (T)0);
+  T run = block_exclusive_scan<T>(loc, wsum, &tot) + pre;
   for (int k = 0; k < kScanItems; k++) {
     run += buf[threadIdx.x * kScanItems + k];
     buf[threadIdx.x * kScanItems + k] = run;
@@ -573,48 +557,44 @@ __global__ void k_scan_apply(const T *in, T *out, int64_t n, const T *boff) {
     if (k < n) out[k + 1] = buf[i];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) out[0] = 0;
+  if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = pre + tot;
 }
 
-template <class T>
-static int exclusive_scan(const T *in, T *out, int64_t n, Scratch &sc, hipStream_t s) {
+constexpr int64_t kScanFlat = 4096;  // block sums that a block adds up itself
+
+template <class T, class F>
+static int exclusive_scan(F f, T *out, int64_t n, Scratch &sc, hipStream_t s, T *total) {
   if (n <= 0) {
-    CEL_HIP(hipMemsetAsync(out, 0, sizeof(T), s));
-    return CEL_OK;
-  }
-  int64_t nb = (n + kScanTile - 1) / kScanTile;
-  if (nb == 1) {
-    k_scan_apply<T><<<1, kScanB, 0, s>>>(in, out, n, nullptr);
+    k_scan_apply<T, F><<<1, kScanB, 0, s>>>(f, out, 0, nullptr, nullptr, total);
     CEL_HIP(hipGetLastError());
     return CEL_OK;
   }
-  T *bsum, *boff;
-  CEL_TRY(sc.get(&bsum, nb));
-  CEL_TRY(sc.get(&boff, nb + 1));
-  k_scan_reduce<T><<<(unsigned)nb, kScanB, 0, s>>>(in, n, bsum);
-  CEL_TRY(exclusive_scan<T>(bsum, boff, nb, sc, s));
-  k_scan_apply<T><<<(unsigned)nb, kScanB, 0, s>>>(in, out, n, boff);
+  int64_t nb = (n + kScanTile - 1) / kScanTile;
+  T *bsum = nullptr, *boff = nullptr;
+  if (nb > 1) {
+    CEL_TRY(sc.get(&bsum, nb));
+    k_scan_reduce<T, F><<<(unsigned)nb, kScanB, 0, s>>>(f, n, bsum);
+    if (nb > kScanFlat) {
+      CEL_TRY(sc.get(&boff, nb + 1));
+      CEL_TRY((exclusive_scan<T, ScanArray<T>>(ScanArray<T>{bsum}, boff, nb, sc, s, nullptr)));
+      bsum = nullptr;
+    }
+  }
+  k_scan_apply<T, F><<<(unsigned)nb, kScanB, 0, s>>>(f, out, n, bsum, boff, total);
   CEL_HIP(hipGetLastError());
   return CEL_OK;
 }
 
-int exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Scratch &sc, hipStream_t s) {
-  return exclusive_scan<int32_t>(in, out, n, sc, s);
+int exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, Scratch &sc, hipStream_t s,
+                       int32_t *total) {
+  return exclusive_scan<int32_t>(ScanArray<int32_t>{in}, out, n, sc, s, total);
 }
-int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, Scratch &sc, hipStream_t s) {
-  return exclusive_scan<int64_t>(in, out, n, sc, s);
+int exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, Scratch &sc, hipStream_t s,
+                       int64_t *total) {
+  return exclusive_scan<int64_t>(ScanArray<int64_t>{in}, out, n, sc, s, total);
 }
 
 // ---------------------------------------------------------------- relabel
-
-__global__ void k_row_deg(int32_t n, const int32_t *order, const int32_t *ptr, int32_t *deg,
-                          const Status *st) {
-  if (failed(st)) return;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    int32_t v = order[p];
-    deg[p] = ptr[v + 1] - ptr[v];
-  }
-}
 
 // Output edges in edge-balanced blocks: slot k of row p (position p) takes
 // edge k - pptr[p] of node order[p], so a row of huge degree is spread over
@@ -632,14 +612,8 @@ __global__ void k_relabel_rows(int32_t n, int32_t m, const int32_t *order, const
 int relabel_csr(int32_t n, int32_t m, const int32_t *order, const int32_t *pos,
                 const int32_t *ptr, const int32_t *idx, int32_t *pptr, int32_t *pidx, Scratch &sc,
                 hipStream_t s, const Status *st) {
-  if (n <= 0) {
-    CEL_HIP(hipMemsetAsync(pptr, 0, sizeof(int32_t), s));
-    return CEL_OK;
-  }
-  int32_t *deg;
-  CEL_TRY(sc.get(&deg, n));
-  k_row_deg<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, order, ptr, deg, st);
-  CEL_TRY(exclusive_scan_i32(deg, pptr, n, sc, s));
+  CEL_TRY(exclusive_scan<int32_t>(ScanRows{order, ptr, st, false}, pptr, n, sc, s, nullptr));
+  if (n <= 0) return CEL_OK;
   k_relabel_rows<<<edge_blocks(m), 256, 0, s>>>(n, m, order, pos, ptr, idx, pptr, pidx, st);
   CEL_HIP(hipGetLastError());
   return CEL_OK;
@@ -662,23 +636,77 @@ __device__ inline bool kless(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib)
   return ka < kb || (ka == kb && ia < ib);
 }
 
-__global__ void k_tile_count(const int32_t *seg, int32_t nseg, int32_t *tcnt, const Status *st) {
-  if (failed(st)) return;  // offsets not validated
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nseg;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t len = seg[i + 1] - seg[i];
-    tcnt[i] = len > 1 ? (len + kSortTile - 1) / kSortTile : 0;
-  }
+// The tile list of segments [s0, s0 + kTileSegs) and the number of tiles
+// before it: one block up to kTileSegs segments; above, the blocks' counts by
+// k_tile_count, and every block adds up the counts before its own.
+constexpr int kTileB = 1024, kTilePer = 16, kTileSegs = kTileB * kTilePer;
+
+__device__ inline int32_t tiles_of(int32_t len) {
+  return len > 1 ? (len + kSortTile - 1) / kSortTile : 0;
 }
 
-__global__ void k_tile_fill(const int32_t *seg, int32_t nseg, const int32_t *toff, Tile *tiles,
-                            const Status *st) {
-  if (failed(st)) return;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nseg;
-       i += (int64_t)gridDim.x * blockDim.x) {
+// the sum of x over the block's waves before this one plus the lanes before
+// this one, and the block's total
+__device__ inline int32_t tile_scan(int32_t x, int32_t *ws, int32_t *total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int32_t inc = x;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t y = __shfl_up(inc, off);
+    if (lane >= off) inc += y;
+  }
+  if (lane == 63) ws[wv] = inc;
+  __syncthreads();
+  int32_t base = 0, tot = 0;
+  for (int i = 0; i < kTileB / 64; i++) {
+    if (i < wv) base += ws[i];
+    tot += ws[i];
+  }
+  __syncthreads();
+  *total = tot;
+  return base + inc - x;
+}
+
+__global__ void __launch_bounds__(kTileB) k_tile_count(const int32_t *seg, int32_t nseg,
+                                                      int32_t *bcnt, const Status *st) {
+  __shared__ int32_t ws[kTileB / 64];
+  const bool ok = !failed(st);  // offsets not validated otherwise
+  const int64_t s0 = (int64_t)blockIdx.x * kTileSegs;
+  int32_t c = 0;
+  for (int k = 0; ok && k < kTilePer; k++) {
+    const int64_t i = s0 + k * kTileB + threadIdx.x;
+    if (i < nseg) c += tiles_of(seg[i + 1] - seg[i]);
+  }
+  int32_t tot;
+  (void)tile_scan(c, ws, &tot);
+  if (threadIdx.x == 0) bcnt[blockIdx.x] = tot;
+}
+
+// tiles in any order (they are sorted one by one); *ntiles = 0 after a failed check
+__global__ void __launch_bounds__(kTileB) k_tile_fill(const int32_t *seg, int32_t nseg,
+                                                     const int32_t *bcnt, Tile *tiles,
+                                                     int32_t *ntiles, const Status *st) {
+  __shared__ int32_t ws[kTileB / 64];
+  const bool ok = !failed(st);
+  const int64_t s0 = (int64_t)blockIdx.x * kTileSegs;
+  int32_t pre = 0;
+  if (bcnt) {
+    int32_t a = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kTileB) a += bcnt[i];
+    (void)tile_scan(a, ws, &pre);
+  }
+  int32_t c = 0;
+  for (int k = 0; ok && k < kTilePer; k++) {
+    const int64_t i = s0 + k * kTileB + threadIdx.x;
+    if (i < nseg) c += tiles_of(seg[i + 1] - seg[i]);
+  }
+  int32_t tot;
+  int32_t t = pre + tile_scan(c, ws, &tot);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *ntiles = ok ? pre + tot : 0;
+  for (int k = 0; ok && k < kTilePer; k++) {
+    const int64_t i = s0 + k * kTileB + threadIdx.x;
+    if (i >= nseg) break;
     const int32_t a = seg[i], len = seg[i + 1] - a;
     if (len <= 1) continue;
-    int32_t t = toff[i];
     for (int32_t o = 0; o < len; o += kSortTile, t++)
       tiles[t] = Tile{a + o, len - o < kSortTile ? len - o : kSortTile};
   }
@@ -800,18 +828,18 @@ __global__ void k_copy_big(const uint64_t *kin, const uint32_t *iin, uint64_t *k
 int segmented_sort(uint64_t *keys, uint32_t *ids, const int32_t *seg, int32_t nseg, int64_t n,
                    Scratch &sc, hipStream_t s, const Status *st) {
   if (nseg <= 0 || n <= 1) return CEL_OK;
-  int32_t *tcnt, *toff;
+  int32_t *bcnt = nullptr, *ntiles;
   Tile *tiles;
   const int64_t maxtiles = (int64_t)nseg + n / kSortTile + 1;
-  CEL_TRY(sc.get(&tcnt, nseg));
-  CEL_TRY(sc.get(&toff, (int64_t)nseg + 1));
+  const unsigned nb = (unsigned)(((int64_t)nseg + kTileSegs - 1) / kTileSegs);
+  CEL_TRY(sc.get(&ntiles, 1));
   CEL_TRY(sc.get(&tiles, maxtiles));
-  k_tile_count<<<grid_for(nseg, 256, 4096), 256, 0, s>>>(seg, nseg, tcnt, st);
-  CEL_TRY(exclusive_scan_i32(tcnt, toff, nseg, sc, s));
-  k_tile_fill<<<grid_for(nseg, 256, 4096), 256, 0, s>>>(seg, nseg, toff, tiles, st);
-  {
-    k_sort_tiles<<<(unsigned)maxtiles, 256, 0, s>>>(keys, ids, tiles, toff + nseg, st);
+  if (nb > 1) {
+    CEL_TRY(sc.get(&bcnt, nb));
+    k_tile_count<<<nb, kTileB, 0, s>>>(seg, nseg, bcnt, st);
   }
+  k_tile_fill<<<nb, kTileB, 0, s>>>(seg, nseg, bcnt, tiles, ntiles, st);
+  k_sort_tiles<<<(unsigned)maxtiles, 256, 0, s>>>(keys, ids, tiles, ntiles, st);
   int passes = 0;  // enough for the longest possible segment (n)
   while (((int64_t)kSortTile << passes) < n) passes++;
   if (passes > 0) {

@@ -750,7 +750,8 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
   uint64_t *nearw;
   uint32_t *hcnt;
   int64_t *cost;
-  CEL_TRY(sc.get(&ncnt, n));
+  CEL_TRY(sc.get(&ncnt, (int64_t)n + 2 + gmax));  // and the barrier's words: cleared together
+  bar = ncnt + n;
   CEL_TRY(sc.get(&nptr, (int64_t)n + 1));
   CEL_TRY(sc.get(&noff, m));
   CEL_TRY(sc.get(&nearw, n));
@@ -758,22 +759,20 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
   CEL_TRY(sc.get(&hoff, (int64_t)n + 1));
   CEL_TRY(sc.get(&Parg, (int64_t)n + 1));
   CEL_TRY(sc.get(&cost, (int64_t)n + 1));
-  CEL_TRY(sc.get(&bar, 2 + (int64_t)gmax));
-  k_fill_i32<<<grid_for(n, 256, 4096), 256, 0, s>>>(ncnt, n, 0);
+  k_fill_i32<<<grid_for((int64_t)n + 2 + gmax, 256, 4096), 256, 0, s>>>(ncnt, (int64_t)n + 2 + gmax,
+                                                                      0);
   k_dpn_count<<<edge_blocks(m), 256, 0, s>>>(n, m, R, sptr, sidx, ncnt, st);
   CEL_TRY(exclusive_scan_i32(ncnt, nptr, n, sc, s));
   k_dpn_fill<<<edge_blocks(m), 256, 0, s>>>(n, m, R, sptr, sidx, nptr, ncnt, noff, st);
   k_dpn_heavy<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, nptr, hflag, st);
-  CEL_TRY(exclusive_scan_i32(hflag, hoff, n, sc, s));
-  int32_t H = 0;  // positions with more than four offsets below R
-  int64_t total = 0;
-  CEL_HIP(hipMemcpyAsync(&H, hoff + n, sizeof H, hipMemcpyDeviceToHost, s));
-  CEL_HIP(hipMemcpyAsync(&total, PO + n, sizeof total, hipMemcpyDeviceToHost, s));
-  CEL_HIP(hipStreamSynchronize(s));
+  CEL_TRY(exclusive_scan_i32(hflag, hoff, n, sc, s, &st->i1));
+  Status hs;
+  CEL_TRY(read_status(st, &hs, s));
+  const int32_t H = hs.i1;  // positions with more than four offsets below R
+  const int64_t total = hs.s1;
   if ((int64_t)H * (R + 1) * 4 > (int64_t(1) << 30)) return CEL_OK;  // tables too large: blocked DP
   CEL_TRY(sc.get(&hcnt, (int64_t)H * (R + 1)));
   k_dpn_pack<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, R, nptr, noff, hoff, nearw, hcnt, st);
-  k_fill_i32<<<1, 256, 0, s>>>(bar, 2 + (int64_t)gmax, 0);
   CEL_HIP(hipGetLastError());
   const double blocked_us = 500.0 + 0.064 * n;  // the blocked DP: 64 ns per target
   // Values that fit 40 bits (S is at most PO[n], the comm of all edges): tiles

@@ -890,7 +890,7 @@ static int makespan_impl(const char *fn, const cel_graph *g, const cel_devices *
                          int64_t *finish, int64_t *makespan, Scratch &sc, hipStream_t s) {
   const int32_t n = g->n;
   Status *st;
-  int32_t *tmp, *pos, *pptr, *pidx;
+  int32_t *pos, *pptr, *pidx;
   int64_t *wp, *cq, *finp;
   uint8_t *devp;
   CEL_TRY(sc.get(&st, 1));
@@ -901,10 +901,8 @@ static int makespan_impl(const char *fn, const cel_graph *g, const cel_devices *
     CEL_HIP(hipStreamSynchronize(s));
     return CEL_OK;
   }
-  CEL_TRY(sc.get(&tmp, n));
   CEL_TRY(sc.get(&pos, n));
-  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, tmp, sc, s));
-  CEL_TRY(check_level_order(g, order, level, level_ptr, L, pos, st, s));
+  CEL_TRY(check_graph_levels(g, d->bw, d->lat, order, level, level_ptr, L, pos, st, sc, s));
   CEL_TRY(sc.get(&pptr, (int64_t)n + 1));
   CEL_TRY(sc.get(&pidx, g->m));
   CEL_TRY(sc.get(&wp, n));

@@ -924,13 +924,11 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
     CEL_HIP(hipStreamSynchronize(s));
     return CEL_OK;
   }
-  int32_t *tmp, *pos, *iptr, *iidx;
+  int32_t *pos, *iptr, *iidx;
   int64_t *wp, *cq, *finp;
   uint8_t *devp;
-  CEL_TRY(sc.get(&tmp, n));
   CEL_TRY(sc.get(&pos, n));
-  CEL_TRY(check_graph(g, bwmin, latmax, true, st, tmp, sc, s));
-  CEL_TRY(check_topo_order(g, order, pos, st, s));
+  CEL_TRY(check_graph_topo(g, bwmin, latmax, true, order, pos, st, sc, s));
   const int64_t Kn = (int64_t)K * n;
   CEL_TRY(sc.get(&iptr, (int64_t)n + 1));
   CEL_TRY(sc.get(&iidx, g->m));
@@ -1097,13 +1095,11 @@ extern "C" int cel_colocate(const cel_graph *g, const int32_t *order, const int3
   if (n == 0) return CEL_OK;
   Scratch sc(s);
   Status *st;
-  int32_t *tmp, *pos, *lead;
+  int32_t *pos, *lead;
   CEL_TRY(sc.get(&st, 1));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
-  CEL_TRY(sc.get(&tmp, n));
   CEL_TRY(sc.get(&pos, n));
-  CEL_TRY(check_graph(g, 1, 0, false, st, tmp, sc, s));
-  CEL_TRY(check_topo_order(g, order, pos, st, s));
+  CEL_TRY(check_graph_topo(g, 1, 0, false, order, pos, st, sc, s));
   if (n_groups > 0) {
     CEL_TRY(sc.get(&lead, n_groups));
     k_fill_i32<<<grid_for(n_groups, 256, 1024), 256, 0, s>>>(lead, n_groups, INT32_MAX);

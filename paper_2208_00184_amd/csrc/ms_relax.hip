@@ -72,11 +72,17 @@ __device__ inline uint64_t same_device_lanes(uint32_t d, bool act) {
 
 // ------------------------------------------------- chain order (counting sort)
 
-// cnt[d * nb + b] = nodes of device d among positions [b kRxCB, (b+1) kRxCB)
+// cnt[d * nb + b] = nodes of device d among positions [b kRxCB, (b+1) kRxCB).
+// Also clears what the kernels after it count in.
 __global__ void __launch_bounds__(kRxCB) k_rx_count(int32_t n, int32_t D, int32_t nb,
                                                    const uint8_t *devp, int32_t *cnt,
-                                                   const Status *st) {
+                                                   int32_t *xcnt, int32_t *bar, int32_t nbar,
+                                                   int64_t *makespan, const Status *st) {
   __shared__ int32_t h[256];
+  const int64_t tid = (int64_t)blockIdx.x * kRxCB + threadIdx.x;
+  if (tid < n) xcnt[tid] = 0;
+  for (int64_t i = tid; i < nbar; i += (int64_t)gridDim.x * kRxCB) bar[i] = 0;
+  if (tid == 0) *makespan = 0;
   if (failed(st)) return;
   for (int i = threadIdx.x; i < D; i += kRxCB) h[i] = 0;
   __syncthreads();
@@ -495,14 +501,11 @@ int ms_relax(const cel_graph *g, const cel_devices *d, int32_t L, const int32_t 
   CEL_TRY(sc.get(&finc, n));
   CEL_TRY(sc.get(&tail, G));
   CEL_TRY(sc.get(&rec, n));
-  k_rx_count<<<nb, kRxCB, 0, s>>>(n, D, nb, devp, cnt, st);
+  k_rx_count<<<nb, kRxCB, 0, s>>>(n, D, nb, devp, cnt, xcnt, bar, 2 + G, makespan, st);
   CEL_TRY(exclusive_scan_i32(cnt, off, (int64_t)D * nb, sc, s));
   k_rx_scatter<<<nb, kRxCB, 0, s>>>(n, D, nb, devp, order, off, g->w, g->ob, g->out_ptr, d->bw,
                                     d->lat, gnode, nslot, wq, cq, st);
   CEL_TRY(exclusive_scan_i64(wq, wxa, n, sc, s));
-  k_fill_i32<<<grid_for(n, 256, 4096), 256, 0, s>>>(xcnt, n, 0);
-  k_fill_i32<<<grid_for(2 + (int64_t)G, 256, 64), 256, 0, s>>>(bar, 2 + (int64_t)G, 0);
-  k_fill_i64<<<1, 64, 0, s>>>(makespan, 1, 0);
   k_rx_xcount<<<edge_blocks(m), 256, 0, s>>>(n, m, g->in_ptr, g->in_idx, node_dev, nslot, xcnt,
                                              st);
   CEL_TRY(exclusive_scan_i32(xcnt, xptr, n, sc, s));

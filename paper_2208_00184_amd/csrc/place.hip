@@ -1244,11 +1244,9 @@ extern "C" int cel_place(const cel_graph *g, const cel_devices *d, const int32_t
     return set_error(CEL_E_NOMEM, "%s: D * n_clusters too large for the busy lists", fn);
   Scratch sc(s);
   Status *st;
-  int32_t *tmp;
   CEL_TRY(sc.get(&st, 1));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
-  CEL_TRY(sc.get(&tmp, n));
-  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, tmp, sc, s));
+  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, sc, s));
   if (C == 0) {
     Status h;
     CEL_TRY(read_status(st, &h, s));
@@ -1258,44 +1256,39 @@ extern "C" int cel_place(const cel_graph *g, const cel_devices *d, const int32_t
     return CEL_OK;
   }
   uint64_t *W, *MEM, *back, *keys;
-  int32_t *cnt, *boff, *ca, *ncp;
+  int32_t *cnt, *cur, *boff, *ca, *ncp;
   int64_t *ecost, *cc, *Fin, *bs, *bf, *dcap;
   uint32_t *ids;
   const int64_t m = g->m;
-  CEL_TRY(sc.get(&W, C));
-  CEL_TRY(sc.get(&MEM, C));
-  CEL_TRY(sc.get(&back, C));
-  CEL_TRY(sc.get(&cnt, C));
+  // sums and cursors in one block, cleared together
+  CEL_TRY(sc.get(&W, 4 * (int64_t)C));
+  MEM = W + C;
+  back = W + 2 * (int64_t)C;
+  cnt = reinterpret_cast<int32_t *>(W + 3 * (int64_t)C);
+  cur = cnt + C;
   CEL_TRY(sc.get(&boff, (int64_t)C + 1));
   CEL_TRY(sc.get(&ncp, C));
   CEL_TRY(sc.get(&Fin, C));
   CEL_TRY(sc.get(&dcap, d->D));
   CEL_TRY(sc.get(&bs, d->D * bcap));
   CEL_TRY(sc.get(&bf, d->D * bcap));
-  CEL_HIP(hipMemsetAsync(W, 0, sizeof(uint64_t) * C, s));
-  CEL_HIP(hipMemsetAsync(MEM, 0, sizeof(uint64_t) * C, s));
-  CEL_HIP(hipMemsetAsync(back, 0, sizeof(uint64_t) * C, s));
-  CEL_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * C, s));
+  CEL_HIP(hipMemsetAsync(W, 0, sizeof(uint64_t) * 4 * C, s));
   CEL_HIP(hipMemcpyAsync(dcap, d->cap, sizeof(int64_t) * d->D, hipMemcpyHostToDevice, s));
   k_place_nodes<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, C, cluster_id, g->w, g->mem, W, MEM, st);
   const unsigned eb = edge_blocks(g->m);
   k_place_edges<0><<<eb, 256, 0, s>>>(*g, d->bw, d->lat, cluster_id, cnt, nullptr, nullptr,
                                       nullptr, nullptr, st);
-  CEL_TRY(exclusive_scan_i32(cnt, boff, C, sc, s));
+  CEL_TRY(exclusive_scan_i32(cnt, boff, C, sc, s, &st->i2));
   Status h;
   CEL_TRY(read_status(st, &h, s));
   if (h.err) return status_error(h, fn);
-  std::vector<int32_t> hb(C + 1);
-  CEL_HIP(hipMemcpyAsync(hb.data(), boff, sizeof(int32_t) * (C + 1), hipMemcpyDeviceToHost, s));
-  CEL_HIP(hipStreamSynchronize(s));
-  const int64_t ncross = hb[C];
+  const int64_t ncross = h.i2;
   CEL_TRY(sc.get(&keys, ncross));
   CEL_TRY(sc.get(&ids, ncross));
   CEL_TRY(sc.get(&ca, ncross + kPlacePad));  // k_place reads up to kPlacePad past a list
   CEL_TRY(sc.get(&cc, ncross + kPlacePad));
   CEL_TRY(sc.get(&ecost, m));
-  CEL_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * C, s));
-  k_place_edges<1><<<eb, 256, 0, s>>>(*g, d->bw, d->lat, cluster_id, cnt, boff, keys, ids, ecost,
+  k_place_edges<1><<<eb, 256, 0, s>>>(*g, d->bw, d->lat, cluster_id, cur, boff, keys, ids, ecost,
                                       st);
   CEL_TRY(segmented_sort(keys, ids, boff, C, ncross, sc, s, st));
   k_place_combine<<<grid_for((int64_t)C * 64, 256, 8192), 256, 0, s>>>(C, boff, keys, ids, ecost,
@@ -1363,14 +1356,12 @@ extern "C" int cel_comm_sums(const cel_graph *g, const cel_devices *d, const int
   if (!edge_comm || !w_sum) return set_error(CEL_E_ARG, "%s: NULL argument", fn);
   Scratch sc(s);
   Status *st;
-  int32_t *tmp;
   unsigned long long *sums;
   CEL_TRY(sc.get(&st, 1));
-  CEL_TRY(sc.get(&tmp, g->n));
   CEL_TRY(sc.get(&sums, 2));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
   CEL_HIP(hipMemsetAsync(sums, 0, 2 * sizeof(unsigned long long), s));
-  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, tmp, sc, s));
+  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, sc, s));
   k_comm_sums<<<edge_blocks(g->m), 256, 0, s>>>(*g, d->bw, d->lat, cluster_id, sums, st);
   CEL_HIP(hipGetLastError());
   unsigned long long h2[2] = {0, 0};
@@ -1396,11 +1387,9 @@ extern "C" int cel_order_place(const cel_graph *g, const cel_devices *d, const i
     return set_error(CEL_E_ARG, "%s: n_clusters = %d out of range", fn, C);
   Scratch sc(s);
   Status *st;
-  int32_t *tmp;
   CEL_TRY(sc.get(&st, 1));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
-  CEL_TRY(sc.get(&tmp, n));
-  CEL_TRY(check_graph(g, d->bw, d->lat, false, st, tmp, sc, s));
+  CEL_TRY(check_graph(g, d->bw, d->lat, false, st, sc, s));
   if (C == 0) {
     Status h;
     CEL_TRY(read_status(st, &h, s));
@@ -1462,11 +1451,9 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
   }
   Scratch sc(s);
   Status *st;
-  int32_t *tmp;
   CEL_TRY(sc.get(&st, 1));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
-  CEL_TRY(sc.get(&tmp, n));
-  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, tmp, sc, s));
+  CEL_TRY(check_graph(g, d->bw, d->lat, true, st, sc, s));
   if (C == 0) {
     Status hs;
     CEL_TRY(read_status(st, &hs, s));
@@ -1543,19 +1530,15 @@ extern "C" int cel_place_ext(const cel_graph *g, const cel_devices *d, const cel
   k_pe_nodes<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, C, U, cluster_id, g->w, g->mem,
                                                     grp ? group : nullptr, lead, umul_d, W2, MEMo,
                                                     fcnt, st);
-  CEL_TRY(exclusive_scan_i32(fcnt, foff, C, sc, s));
+  CEL_TRY(exclusive_scan_i32(fcnt, foff, C, sc, s, &st->i3));
   const unsigned eb = edge_blocks(g->m);
   k_place_edges<0><<<eb, 256, 0, s>>>(*g, d->bw, d->lat, cluster_id, cnt, nullptr, nullptr,
                                       nullptr, nullptr, st);
-  CEL_TRY(exclusive_scan_i32(cnt, boff, C, sc, s));
+  CEL_TRY(exclusive_scan_i32(cnt, boff, C, sc, s, &st->i2));
   Status hs;
   CEL_TRY(read_status(st, &hs, s));
   if (hs.err) return status_error(hs, fn);
-  int32_t counts[2];  // coarse-edge slots, followers
-  CEL_HIP(hipMemcpyAsync(&counts[0], boff + C, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  CEL_HIP(hipMemcpyAsync(&counts[1], foff + C, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  CEL_HIP(hipStreamSynchronize(s));
-  const int64_t ncross = counts[0], nfol = counts[1];
+  const int64_t ncross = hs.i2, nfol = hs.i3;  // coarse-edge slots, followers
   CEL_TRY(sc.get(&keys, ncross));
   CEL_TRY(sc.get(&ids, ncross));
   CEL_TRY(sc.get(&ca, ncross));

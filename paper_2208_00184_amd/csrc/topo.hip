@@ -532,7 +532,7 @@ extern "C" int cel_topo_levels(const cel_graph *g, int32_t *level, int32_t *orde
   CEL_TRY(sc.get(&st, 1));
   CEL_TRY(sc.get(&cnt, n));
   CEL_HIP(hipMemsetAsync(st, 0, sizeof(Status), s));
-  CEL_TRY(check_graph(g, 1, 0, /*bound=*/false, st, cnt, sc, s));
+  CEL_TRY(check_graph(g, 1, 0, /*bound=*/false, st, sc, s));
   if (n >= kTopoPolicyN && policy_iteration_on()) {
     // levels by policy iteration over the predecessors
     int64_t *wv, *val;
@@ -572,11 +572,9 @@ extern "C" int cel_topo_levels(const cel_graph *g, int32_t *level, int32_t *orde
   }
   int2 *deg;
   int4 *adj;
-  int32_t *cmax;
   CEL_TRY(sc.get(&deg, n));
   CEL_TRY(sc.get(&adj, n));
-  CEL_TRY(sc.get(&cmax, 1));
-  CEL_HIP(hipMemsetAsync(cmax, 0, sizeof(int32_t), s));
+  int32_t *cmax = &st->i4;  // cleared with the status
   if (n > 0) {
     k_kahn_cnt<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, g->in_ptr, g->in_idx, cnt, cmax, st);
     k_kahn_prep<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, g->out_ptr, g->out_idx, cnt, deg, adj,
