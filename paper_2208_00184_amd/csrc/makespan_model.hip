@@ -18,10 +18,17 @@
 //     during the previous window.  Rows with many inputs are folded by the
 //     whole wave.
 //  B. the window splits into segments, runs of consecutive slots with no
-//     edge among them, taken in order.  A segment's slots add their inputs
-//     from earlier segments (shuffles), then are placed: with FIFO devices
-//     by one segmented max-plus scan over the slots sorted by (device,
-//     position); with insertion by lane d for device d's slots, in order.
+//     edge between devices among them, taken in order.  A segment's slots add
+//     their inputs from earlier segments (shuffles), then are placed by one
+//     segmented max-plus scan over the slots sorted by (device, position).
+//     With insertion that is a guess, every slot after its device's last
+//     task, right up to the first slot that an idle gap ends after; that one
+//     is placed by lane d for its device d, and so are, in order, the slots
+//     of segments with no edge at all where guessing does not pay.  (Placed
+//     clusters leave few nodes to gaps: 16 placements of 55,003 nodes on 8
+//     devices, 877 segments a placement and no miss, where every edge ended a
+//     segment and every slot was placed by itself 7,775 and 54,387; 17.9 ->
+//     2.5 ms.  Devices at random, node by node: 2 to 4 % slower.)
 //     Device d's state (free time or end of its last task, gap count and
 //     ring head, channel free times) lives in lane d.  The segment's
 //     transfers are then issued in slot order.
@@ -169,6 +176,12 @@ __device__ inline void fold_inputs(const MmArgs &a, const uint8_t *dev, const in
 }
 
 constexpr int kTail = 64;  // most recent idle gaps of each device kept in LDS
+// A window is guessed (every slot after its device's last task) where some
+// device has kInsRun of its 64 slots: a guess is some 500 instructions whatever
+// it places, a slot by itself 360 ns, but each device's lane places its own.
+// Windows with kInsMiss slots in gaps stop guessing, and so do up to kInsHold
+// windows after them, twice as many each time.
+constexpr int kInsRun = 24, kInsMiss = 3, kInsHold = 64;
 
 // Device d's idle gaps: the full sorted list in global memory (A / B [0, G),
 // written through), and its newest t = min(G, kTail) entries again in an LDS
@@ -455,6 +468,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
   int64_t gbase = INS && lane < a.D ? a.goff[k * a.D + lane] : 0;
   int32_t ghead = 0;  // ring head of the gap tail
   int64_t snd = 0, rcv = 0, tcur = 0;
+  int32_t careful = 0, hold = 1;  // windows to place one slot at a time (insertion)
   int64_t span = 0;
   uint32_t bad = 0;
   // A slot's own values and its first 4 inputs depend on nothing computed
@@ -534,13 +548,35 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
     load_own(P0 + 64);
     int64_t finw = 0;
     const int64_t wd = HET ? dur_on(w, __shfl(tmr, dv)) : w;  // slot duration on its device
+    // The in-window inputs that end a segment.  One on the slot's own device
+    // ends none: it finishes by the time the device's last task does.  With
+    // insertion a slot without duration is outside that order.
+    uint64_t cmsk = msk;
+    bool guess = false;  // enough slots on one device to place them all at once
+    if (!BLOCK && careful == 0) {
+      uint64_t own = __ballot(act);
+      for (int b = 0; b < 6; b++) {
+        const uint64_t x = __ballot((dv >> b) & 1);
+        own &= (dv >> b) & 1 ? x : ~x;
+      }
+      if (INS) {
+        guess = __ballot(act && __builtin_popcountll(own) >= kInsRun) != 0;
+        own &= __ballot(wd != 0);
+      }
+      if (!INS || wd != 0) cmsk &= ~own;
+    }
+    int miss = 0;        // segments of this window that held a slot for a gap
+    bool skip = false;   // the next segment starts with one
     for (int32_t s0 = 0; s0 < nw;) {
-      const uint64_t cut = __ballot(lane > s0 && lane < nw && (msk & ~below(s0)) != 0);
-      const int32_t s1 = cut ? __builtin_ctzll(cut) : nw;
-      const bool inseg = lane >= s0 && lane < s1;
+      const bool spec = INS && guess && miss < kInsMiss && !skip;
+      skip = false;
+      const uint64_t cm = INS && !spec ? msk : cmsk;
+      const uint64_t cut = __ballot(lane > s0 && lane < nw && (cm & ~below(s0)) != 0);
+      int32_t s1 = cut ? __builtin_ctzll(cut) : nw;
+      bool inseg = lane >= s0 && lane < s1;
       CEL_TCOUNT(11);
       int64_t r = ext;  // + inputs from the earlier segments of this window
-      for (uint64_t mm = inseg ? msk : 0; __ballot(mm != 0);) {
+      for (uint64_t mm = inseg ? msk & below(s0) : 0; __ballot(mm != 0);) {
         const bool has = mm != 0;
         const int q = has ? __builtin_ctzll(mm) : lane;
         mm &= mm - 1;
@@ -588,9 +624,124 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
         s0 = s1;
         continue;
       }
-      if (inseg) atomicOr(&s_lst[dv], 1ull << lane);
-      wave_lds_sync();
-      uint64_t mine = lane < a.D ? s_lst[lane] : 0;
+      bool placed = false;
+      while (INS && spec && !placed) {
+        // Every slot after its device's last task, as FIFO devices have it:
+        // right for all slots that no idle gap ends after.
+        const int32_t d0 = __builtin_amdgcn_readlane(dv, s0);
+        const bool uni = __ballot(inseg && dv != d0) == 0;
+        // sorted by (device, position); one device: as they are
+        int32_t jj = lane, dd = d0, head = s0, rank = lane, first = 0, end = 0;
+        bool val = inseg, fl1 = lane == s0;
+        int64_t rr = r, ww = wd;
+        if (!uni) {
+          if (inseg) atomicOr(&s_lst[dv], 1ull << lane);
+          wave_lds_sync();
+          const int32_t cnt = lane < a.D ? __builtin_popcountll(s_lst[lane]) : 0;
+          end = cnt;
+          for (int off = 1; off < 64; off <<= 1) {
+            const int32_t o = __shfl_up(end, off);
+            if (lane >= off) end += o;
+          }
+          first = end - cnt;
+          const int32_t fd = __shfl(first, dv);
+          if (inseg) {
+            rank = fd + __builtin_popcountll(s_lst[dv] & below(lane));
+            s_fin[rank] = lane;
+          }
+          wave_lds_sync();
+          val = lane < s1 - s0;
+          jj = val ? (int32_t)s_fin[lane] : lane;
+          lds_order();
+          s_lst[lane] = 0;
+          dd = __shfl(dv, jj);
+          rr = __shfl(r, jj);
+          ww = __shfl(wd, jj);
+          head = __shfl(first, dd);
+          fl1 = val && lane == head;
+        }
+        const bool nz = val && ww != 0;
+        int64_t ma = nz ? rr + ww : kNeg, mb = nz ? ww : 0;
+        int32_t fl = fl1 ? 1 : 0;
+        wave_seg_scan_dpp(ma, mb, fl);
+        const int64_t l0 = uni ? readlane64(last, d0) : __shfl(last, dd);
+        const int64_t fs = ma > l0 + mb ? ma : l0 + mb;  // the device's last end after the slot
+        const int64_t fu = __shfl_up(fs, 1);
+        const bool open = nz && rr > (fl1 ? l0 : fu);  // leaves an idle gap before it
+        const uint64_t ob = __ballot(open);
+        const uint64_t prev = ob & below(lane) & ~below(head);
+        const int64_t gl0 = uni ? readlane64(glast, d0) : __shfl(glast, dd);
+        int64_t gx = gl0;  // end of the device's last gap before the slot
+        if (ob) {
+          const int64_t x = __shfl(rr, prev ? 63 - __builtin_clzll(prev) : lane);
+          if (prev) gx = x;
+        }
+        const int64_t fo = nz ? fs : rr;
+        const int64_t myf = uni ? fo : __shfl(fo, rank);
+        if (__ballot(nz && rr < gx)) {  // unless an input of this segment comes later
+          const int64_t myg = uni ? gx : __shfl(gx, rank);
+          int64_t rx = r;
+          for (uint64_t mm = inseg ? msk & ~below(s0) : 0; __ballot(mm != 0); mm &= mm - 1) {
+            const int64_t fq = __shfl(myf, mm ? __builtin_ctzll(mm) : lane);
+            if (mm && fq > rx) rx = fq;
+          }
+          const uint64_t hit = __ballot(inseg && wd != 0 && rx < myg);
+          if (hit) {  // the first slot that a gap may hold: place those before it again
+            CEL_TCOUNT(15);
+            miss++;
+            const int32_t v = __builtin_ctzll(hit);
+            if (v == s0) break;
+            skip = true;
+            s1 = v;
+            inseg = lane >= s0 && lane < s1;
+            continue;
+          }
+        }
+        placed = true;
+        if (inseg) finw = myf;
+        if (ob) {  // the new gaps, in their devices' order
+          const int32_t G = __shfl(gcnt, dd), hd = __shfl(ghead, dd);
+          const int64_t gb = __shfl(gbase, dd);
+          const int32_t gi = G + __builtin_popcountll(prev);
+          const int32_t slot = gi < kTail ? gi : (hd + gi - (G > kTail ? G : kTail)) & (kTail - 1);
+          if (open) {
+            const int64_t from = fl1 ? l0 : fu;
+            a.ga[gb + gi] = from;
+            a.gb[gb + gi] = rr;
+            s_ta[dd * kTail + slot] = from;
+            s_tb[dd * kTail + slot] = rr;
+          }
+          lds_order();
+          // (the device's slots: [first, end), end up to 64)
+          const uint64_t mo = uni ? (lane == d0 ? ob : 0)
+                                  : end > first ? ob & (~uint64_t(0) >> (64 - end)) & ~below(first) : 0;
+          const int64_t gn = __shfl(rr, mo ? 63 - __builtin_clzll(mo) : lane);
+          if (mo) {
+            const int32_t g2 = gcnt + __builtin_popcountll(mo);
+            if (g2 > kTail)
+              ghead = (ghead + g2 - (gcnt > kTail ? gcnt : kTail)) & (kTail - 1);
+            gcnt = g2;
+            glast = gn;
+          }
+        }
+        if (uni) {
+          last = setlane<int64_t>(last, readlane64(fs, s1 - 1), d0);
+        } else {
+          const int64_t nl = __shfl(fs, end > first ? end - 1 : 0);
+          if (end > first) last = nl;
+        }
+      }
+      if (INS && spec && !placed) {  // by gaps, up to the next edge of any kind
+        const uint64_t c2 = __ballot(lane > s0 && lane < nw && (msk & ~below(s0)) != 0);
+        s1 = c2 ? __builtin_ctzll(c2) : nw;
+        inseg = lane >= s0 && lane < s1;
+      }
+      uint64_t mine = 0;
+      if (!placed) {
+        if (inseg) atomicOr(&s_lst[dv], 1ull << lane);
+        wave_lds_sync();
+        mine = lane < a.D ? s_lst[lane] : 0;
+      }
       if (!INS) {
         // FIFO devices: a device's chain last' = max(r, last) + w composes
         // maps x -> max(r + w, x + w); with the segment's slots sorted by
@@ -630,7 +781,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
         lds_order();
         s_lst[lane] = 0;
         mine = 0;
-      } else {
+      } else if (!placed) {
         lds_order();
         s_lst[lane] = 0;
       }
@@ -673,7 +824,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
         }
         if (has) s_fin[j] = f;
       }
-      if (INS) {
+      if (INS && !placed) {
         wave_lds_sync();
         if (inseg) finw = s_fin[lane];
         lds_order();
@@ -703,6 +854,16 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
         }
       }
       s0 = s1;
+    }
+    if (INS) {  // many slots in gaps: the next windows one slot at a time
+      if (careful > 0) {
+        careful--;
+      } else if (miss >= kInsMiss) {
+        careful = hold;
+        hold = hold < kInsHold ? 2 * hold : kInsHold;
+      } else if (guess) {
+        hold = hold > 1 ? hold >> 1 : 1;
+      }
     }
     if (act) span = finw > span ? finw : span;
     // C: finish times of the window

@@ -1,0 +1,105 @@
+"""GPU parity of the insertion models against the CPU oracle, tolerance 0,
+where a window's slots are first placed after their devices' last tasks:
+windows of one and of many devices, chains inside a window on one device, gaps
+that later nodes fill, split and fill exactly, nodes without duration, more
+gaps of a device than its ring keeps, and orders that alternate between long
+runs without a gap and runs of nothing else."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # collected on CPU, skipped there
+    pytest.skip("needs a ROCm GPU", allow_module_level=True)
+
+import paper_2208_00184_amd as cel  # noqa: E402
+from oracle import oracle as O  # noqa: E402
+from workloads import from_edges  # noqa: E402
+
+DEV = "cuda:0"
+MODELS = [cel.MODEL_INSERT, cel.MODEL_INSERT | cel.MODEL_COMM_TASKS]
+
+
+def check(wl, P, model, **het):
+    g, d = cel.Graph.from_arrays(wl, DEV), cel.Devices.from_arrays(wl)
+    order = np.arange(wl.n, dtype=np.int32)
+    P = np.ascontiguousarray(P, np.uint8)
+    ms, st, fi = cel.makespan_model(g, d, torch.from_numpy(order).to(DEV), torch.from_numpy(P).to(DEV), model,
+                                    want_times=True, **het)
+    rm, rs, rf = O.makespan_model(wl, order, P, model, **het)
+    assert np.array_equal(fi.cpu().numpy(), rf) and np.array_equal(st.cpu().numpy(), rs), model
+    assert np.array_equal(ms.cpu().numpy(), rm), model
+
+
+def dag(n, D, seed, reach, w, ob, zero=0.0, free=0.1):
+    """In-edges from up to `reach` nodes back; a share `free` of nodes without
+    inputs (ready at once, so that any gap may take them), `zero` without duration."""
+    rng = np.random.default_rng([seed, n, D, reach])
+    k = np.where(rng.random(n) < free, 0, rng.integers(1, 4, n))
+    k[0] = 0
+    dst = np.repeat(np.arange(n), k)
+    src = dst - 1 - (rng.random(dst.size) * np.minimum(dst, reach)).astype(np.int64)
+    e = np.stack([src, dst], 1)
+    wt = rng.integers(*w, n)
+    wt[rng.random(n) < zero] = 0
+    return from_edges(n, e[src >= 0], wt, rng.integers(*ob, n), D, [10 ** 15] * D, 7, 3)
+
+
+def placements(n, D, seed):
+    rng = np.random.default_rng([seed, n, D])
+    return np.stack([np.repeat(rng.integers(0, D, n // r + 1), r)[:n] for r in (1, 5, 64, 100, 1000)])
+
+
+@pytest.mark.parametrize("model", MODELS)
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 3000])
+@pytest.mark.parametrize("zero,free", [(0.0, 0.0), (0.3, 0.02), (0.0, 0.4), (0.6, 0.6)])
+def test_insert_windows(model, n, zero, free):
+    for D, reach, ob in ((1, 5, (0, 400)), (3, 4, (0, 4000)), (8, 200, (0, 40)), (64, 30, (0, 400))):
+        P = placements(n, D, 1)
+        check(dag(n, D, 2, reach, (1, 60), ob, zero, free), P, model)
+        rng = np.random.default_rng([n, D])
+        het = dict(tmul=[int(x) for x in rng.integers(1, 4096, D)], bw=rng.integers(1, 40, (D, D)).tolist(),
+                   lat=rng.integers(0, 50, (D, D)).tolist())
+        check(dag(n, D, 3, reach, (1, 60), ob, zero, free), P[1:4], model, **het)
+
+
+@pytest.mark.parametrize("model", MODELS)
+def test_exact_fills_and_full_rings(model):
+    """Transfers of 13 leave gaps of a few units on two devices, hundreds of
+    them; later nodes of one to nine units split, fill and pass them by."""
+    n = 4000
+    wl = dag(n, 2, 5, 3, (1, 10), (50, 80), 0.05, 0.0)
+    late = dag(n, 2, 6, 3, (1, 10), (50, 80), 0.05, 0.9)
+    e = [np.stack([np.repeat(np.arange(n), np.diff(x.out_ptr)), x.out_idx], 1) + s for x, s in ((wl, 0), (late, n))]
+    both = from_edges(2 * n, np.concatenate(e), np.concatenate([wl.w, late.w]), np.concatenate([wl.ob, late.ob]), 2,
+                      [10 ** 15] * 2, 7, 3)
+    check(both, placements(2 * n, 2, 7), model)
+
+
+@pytest.mark.parametrize("model", MODELS)
+def test_runs_with_and_without_gaps(model):
+    """Chains on one device, then free nodes, in turn: guesses hold, fail and hold again."""
+    n, D = 6000, 4
+    rng = np.random.default_rng(8)
+    free = (np.arange(n) // 300) % 2 == 1
+    v = np.arange(1, n)
+    e = np.stack([v - 1 - rng.integers(0, np.minimum(v, 3)), v], 1)
+    wl = from_edges(n, e[~free[1:]], rng.integers(1, 30, n), rng.integers(0, 300, n), D, [10 ** 15] * D, 7, 3)
+    check(wl, placements(n, D, 9), model)
+
+
+@pytest.mark.parametrize("model", MODELS)
+def test_full_windows(model):
+    """No edge inside a window: 64 slots at once on up to 64 devices."""
+    n = 64 * 40
+    rng = np.random.default_rng(10)
+    v = np.arange(64, n)
+    e = np.concatenate([np.stack([(v // 64) * 64 - 1 - rng.integers(0, np.minimum((v // 64) * 64, 150)), v], 1)
+                        for _ in range(2)])
+    for D in (1, 2, 5, 64):
+        wl = from_edges(n, e, rng.integers(0, 30, n), rng.integers(0, 600, n), D, [10 ** 15] * D, 7, 3)
+        check(wl, placements(n, D, 11), model)
