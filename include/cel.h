@@ -336,8 +336,8 @@ int cel_kernel_stats(char *buf, int buflen, int reset);
  * chain makes edges inside one device redundant), exact after *rounds rounds,
  * the last of which changed nothing; 1: K = 1 by the level sweep, after
  * *rounds rounds of relaxation that did not converge within their budget (0
- * when the relaxation could not be launched); 2: K > 1 (level sweeps of the
- * batch), *rounds = 0.
+ * when the relaxation could not be launched); 2: K > 1 (a batch: level sweeps,
+ * or blocks of tasks where the levels are narrow), *rounds = 0.
  * Outputs: path, rounds (host).
  * Errors: CEL_E_ARG (NULL argument). */
 int cel_makespan_info(int32_t *path, int32_t *rounds);

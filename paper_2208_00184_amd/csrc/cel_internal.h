@@ -711,6 +711,7 @@ struct MsBlocks {
   const uint64_t *dmask;
   int64_t transfers;
   int64_t *finp, *makespan;
+  uint32_t *info;               // [K n] without transfers: room for the tasks' words, or NULL
   const char *timer;
 };
 int ms_blocks(const MsBlocks &b, class Scratch &sc, hipStream_t s, Status *st);

@@ -188,6 +188,15 @@ __device__ inline void wave_scan_maxplus_z(int64_t &a, int64_t &b) {
 }
 constexpr int kBatchWide = 384;  // batches up to this size get one CU-sized window per placement
 constexpr int kWideLevels = 256;  // mean level width from which batches skip the windows
+// Batches over narrow levels (mean width up to kBlocksWidth, kBlocksMin nodes
+// and more) run in blocks of tasks in LDS (ms_blocks.hip): their time follows
+// the nodes (some 7 ns each), the ring's the levels (0.45 to 0.85 us each).
+// Whole calls of 64 placements, ring -> blocks: inception-600 (width 8) 3,409 ->
+// 483 us, transformer-24 (width 10) 1,043 -> 362; layered graphs of width 37
+// 434 -> 443 (2 placements 427 -> 400, scattered ones 803 -> 491), of 46
+// (2,048 nodes) 177 -> 145; transformer-96 (width 101) 10,295 -> 10,943.
+// 1,670 nodes: 287 -> 136.
+constexpr int32_t kBlocksWidth = 48, kBlocksMin = 1024;
 
 template <int B, int NC, int EC>
 __global__ void __launch_bounds__(B)
@@ -990,6 +999,41 @@ static int makespan_impl(const char *fn, const cel_graph *g, const cel_devices *
       k_makespan_levels<512, 1, 3><<<(unsigned)K, 512, 0, s>>>(n, L, dbits, level_ptr, pptr, pidx,
                                                               wp, cq, devp, finp, makespan, st);
     } else if (K <= kBatchWide) {
+      // Narrow levels: the FIFO schedule in blocks of tasks in LDS; the ring
+      // when values may reach 2^47 or the blocks need more iterations (1.2 us
+      // and more each) than the ring takes.
+      if ((int64_t)n <= (int64_t)kBlocksWidth * L && n >= kBlocksMin &&
+          (int64_t)K * n <= kBkMaxTasks) {
+        const Scratch::Mark mk = sc.mark();
+        int4 *ipre;
+        CEL_TRY(sc.get(&ipre, n));
+        k_mm_ipre<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, pptr, pidx, ipre, st);
+        MsBlocks b{};
+        b.K = K;
+        b.n = n;
+        b.D = d->D;
+        b.budget = 128 + L / 2;
+        b.iptr = pptr;
+        b.iidx = pidx;
+        b.ipre = ipre;
+        b.wp = wp;
+        b.cq = cq;
+        b.devp = devp;
+        b.finp = finp;
+        b.info = (uint32_t *)(finp + (int64_t)K * n);  // the ring's fin + c: unused here
+        b.makespan = makespan;
+        b.timer = "k_makespan_batch";
+        CEL_TRY(ms_blocks(b, sc, s, st));
+        if (start || finish)
+          k_makespan_out<<<grid_for((int64_t)K * n, 256, 8192), 256, 0, s>>>(
+              K, n, order, finp, wp, start, finish, st);
+        CEL_HIP(hipGetLastError());
+        Status hb;
+        CEL_TRY(read_status(st, &hb, s));
+        if (hb.err) return status_error(hb, fn);
+        if (!hb.i1) return CEL_OK;
+        sc.release(mk);
+      }
       CEL_TRY(mb_ring(K, n, g->m, L, level_ptr, order, level, pptr, pidx, wp, cq, devp, finp,
                       finp + (int64_t)K * n, makespan, sc, s, st));
     } else {

@@ -1,5 +1,6 @@
-// Makespans of K placements under the device models without insertion, one
-// workgroup each, in blocks of tasks in LDS.
+// Makespans of K placements under the device models without insertion (and of
+// batches of placements over narrow levels, cel_makespan), one workgroup each,
+// in blocks of tasks in LDS.
 //
 // Without insertion every start time is the later of a few finish times fixed
 // by the order alone: a node waits for the previous node on its device and for
@@ -614,12 +615,12 @@ int ms_blocks(const MsBlocks &b, Scratch &sc, hipStream_t s, Status *st) {
   a.dmask = b.dmask;
   a.makespan = b.makespan;
   const bool het = b.tmul != nullptr;
-  uint32_t *info;
+  uint32_t *info = b.info;
   const int gy = b.K < 1024 ? b.K : 1024;
   if (!b.aoff) {
     a.nk = b.D;
     a.val = b.finp;
-    CEL_TRY(sc.get(&info, Kn));
+    if (!info) CEL_TRY(sc.get(&info, Kn));
     k_bk_prev<false><<<dim3((b.n + kBkB - 1) / kBkB, b.K), kBkT, 0, s>>>(b.n, b.D, b.devp, nullptr,
                                                                         nullptr, info, st);
   } else {

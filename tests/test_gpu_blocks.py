@@ -1,5 +1,5 @@
 """GPU parity of the makespans taken in blocks of tasks in LDS (the device
-models without insertion) against the CPU oracle, tolerance 0: task counts around the blocks of 2,048, rows of
+models without insertion; batches of placements over narrow levels) against the CPU oracle, tolerance 0: task counts around the blocks of 2,048, rows of
 more than four and sixteen inputs in and before the block, blocks whose listed
 inputs do not fit (taken again at half the size), long chains of one device,
 every model with and without heterogeneous devices, and values past the packed
@@ -123,3 +123,48 @@ def test_alternating_channels():
     P = (np.arange(n) % 2).astype(np.uint8)[None, :]
     for model in (0, cel.MODEL_COMM_TASKS, cel.MODEL_COMM_BLOCK):
         check_model(wl, P, model)
+
+
+def check_batch(wl, P, seed=0):
+    """cel.makespan of a batch, with and without its own allocations, in level
+    order with the ids shuffled inside each level."""
+    lev, _, lp, L = O.topo_levels(wl)
+    order = np.lexsort((np.random.default_rng(seed).permutation(wl.n), lev)).astype(np.int32)
+    g, d = cel.Graph.from_arrays(wl, DEV), cel.Devices.from_arrays(wl)
+    args = (tt(order, np.int32), tt(lev, np.int32), tt(lp, np.int32), L, tt(P, np.uint8))
+    rm, rs, rf = O.makespan(wl, order, P)
+    for fixed in (False, True):
+        ms, st, fi = cel.makespan(g, d, *args, want_times=True, noalloc=fixed)
+        assert np.array_equal(ms.cpu().numpy(), rm), (wl.n, L, fixed)
+        assert np.array_equal(fi.cpu().numpy(), rf) and np.array_equal(st.cpu().numpy(), rs), (wl.n, L, fixed)
+        ms, st, fi = cel.makespan(g, d, *args, noalloc=fixed)
+        assert np.array_equal(ms.cpu().numpy(), rm) and st is None and fi is None
+    return L
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 2047, 2048, 2049, 4097, 9000])
+@pytest.mark.parametrize("D", [1, 2, 16, 64, 65, 255])
+def test_batches_of_placements(n, D):
+    L = check_batch(dag(n, D, 12, reach=60), placements(n, D, 5, 12), n)
+    assert n <= 48 * L  # narrow enough for the blocks (from 1,024 nodes on)
+
+
+@pytest.mark.parametrize("width", [47, 48, 49])
+def test_batches_by_level_width(width):
+    """Full levels of one width, each node fed by two of the level before."""
+    n = 40 * width
+    v = np.arange(width, n)
+    rng = np.random.default_rng(width)
+    e = np.concatenate([np.stack([(v // width - 1) * width + rng.integers(0, width, v.size), v], 1) for _ in range(2)])
+    wl = from_edges(n, e, rng.integers(0, 60, n), rng.integers(0, 400, n), 8, [10 ** 15] * 8, 7, 3)
+    assert check_batch(wl, placements(n, 8, 6, 13)) == 40
+
+
+def test_batches_at_the_limits():
+    """Values past the packed words (the ring runs); hubs whose inputs do not
+    fit beside their block; more scattered placements than CUs."""
+    check_batch(dag(2500, 4, 14, ob_max=1 << 40, w_max=1 << 45, reach=60), placements(2500, 4, 4, 14))
+    check_batch(dag(9000, 6, 15, fan=40, reach=90, hubs=((4000, 3000), (8191, 17000))), placements(9000, 6, 4, 15))
+    n, rng = 3000, np.random.default_rng(16)
+    L = check_batch(dag(n, 3, 16, reach=20, ob_max=4000, w_max=3), rng.integers(0, 3, (300, n)).astype(np.uint8))
+    assert n <= 48 * L
