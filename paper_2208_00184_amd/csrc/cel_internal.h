@@ -60,6 +60,14 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
+// A workgroup barrier after which the workgroup reads its waves' earlier
+// global stores: each wave waits for its own (vmcnt(0)) before it arrives.
+__device__ inline void store_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
 
 // ------------------------------------------------ wave-level scans with DPP
 // DPP moves read another lane's register inside the VALU (no LDS round trip).

@@ -331,8 +331,8 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
   for (int32_t p0 = 0, lim = kBkB, par = 0; p0 < N;) {
     uint64_t *const s_e = s_ent[par];
     const uint64_t *const s_pe = s_ent[par ^ 1];
-    // a final value before the block: the previous block's are read from LDS,
-    // older ones were stored before the last full barrier
+    // a final value before the block: the previous block's are read from LDS;
+    // older ones were complete before the previous block's store_barrier
     auto final_val = [&](int32_t x) -> int64_t {
       return x >= pp0 ? (int64_t)(s_pe[x - pp0] >> 16) : val[x];
     };
@@ -405,7 +405,6 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
       if (du != d) b = max_nonneg(b, v + edge(c, du, d));
       return kEnd;
     };
-    bool over = false;
 #pragma unroll
     for (int u = 0; u < kBkU; u++) {
       const int32_t d = (int32_t)(kk[u] & 255u);
@@ -433,10 +432,7 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
       if (row && !heavy) {
         const int32_t e0 = a.iptr[hp] + (XFER ? 0 : 4), e1 = a.iptr[hp + 1];
         int32_t o = 0, m = 0;
-        if (nt > 1) {
-          o = atomicAdd(&s_ovn, e1 - e0);
-          over |= o + (e1 - e0) > kBkOv;
-        }
+        if (nt > 1) o = atomicAdd(&s_ovn, e1 - e0);
         for (int32_t e = e0; e < e1; e++) {
           const uint32_t s = input(XFER ? xtask(a.iidx[e], d) : a.iidx[e], d, base[u]);
           if (s != kEnd && o + m < kBkOv) s_ov[o + m++] = (uint16_t)s;
@@ -451,7 +447,6 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
         if (nt > 1) {
           if (lane == l) o = atomicAdd(&s_ovn, e1 - e0);
           o = __builtin_amdgcn_readlane(o, l);
-          over |= o + (e1 - e0) > kBkOv;
         }
         int64_t b = 0;
         for (int32_t e = e0; e < e1; e += 64) {
@@ -469,8 +464,12 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
         }
       }
     }
-    if (__syncthreads_or(over)) {  // too many listed inputs: half the tasks (nt = 1 lists none)
+    // The previous block's values, stored about a block ago, are complete
+    // behind this barrier: the next block reads them from memory.
+    store_barrier();
+    if (s_ovn > kBkOv) {  // too many listed inputs: half the tasks (nt = 1 lists none)
       lim = nt / 2 > 0 ? nt / 2 : 1;
+      lds_barrier();  // every wave has read s_ovn before it is cleared
       continue;
     }
     // ---- policy iteration (LDS barriers only: the next block's data is on its way)
