@@ -31,7 +31,10 @@
  *    makespan (eq. 7).  All results are exact integers, hence deterministic.
  *  - Return value: CEL_OK or a negative CEL_E_* code; cel_last_error() gives a
  *    message for the calling thread.  Outputs are unspecified after an error.
- *  - Calls on the same device may run concurrently on different streams.
+ *  - Calls on the same device may run concurrently on different streams.  The
+ *    stretches of a call that spread one kernel over the whole GPU take turns
+ *    between host threads; a call that has waited a second for its turn goes
+ *    on without such a kernel (slower, the same results).
  */
 #ifndef CEL_H
 #define CEL_H

@@ -148,12 +148,13 @@ extern "C" int cel_blevel(const cel_graph *g, const cel_devices *d, const int32_
     CEL_TRY(relabel_csr(n, g->m, order_id, pos, g->in_ptr, g->in_idx, pptr, pidx, sc, s, st));
   }
   bool lb = false, lt = false;
+  GridTurn turn(s);
   if (policy_iteration_on()) {
     CEL_TRY(lp_policy(n, g->m, L, 0, sptr, sidx, wv, 0, blp, &st->i0, "k_blevel_policy", sc, s,
-                      st, &lb));
+                      st, turn, &lb));
     if (tlp)
       CEL_TRY(lp_policy(n, g->m, L, 0, pptr, pidx, wv, 1, tlp, &st->i2, "k_tlevel_policy", sc, s,
-                        st, &lt));
+                        st, turn, &lt));
   }
   bool sweep_b = true, sweep_t = tlp != nullptr;
   t_bl_info = {1, 0, tlp ? 1 : 2, 0};
@@ -181,6 +182,7 @@ extern "C" int cel_blevel(const cel_graph *g, const cel_devices *d, const int32_
     CEL_TRY(outputs(true, true, s, s));
     Status h;
     CEL_TRY(read_status(st, &h, s));
+    turn.done();
     if (h.err) return status_error(h, fn);
     if (h.i0 && (!tlp || h.i2)) {
       t_bl_info = {0, h.i1, tlp ? 0 : 2, tlp ? h.i3 : 0};
@@ -191,6 +193,7 @@ extern "C" int cel_blevel(const cel_graph *g, const cel_devices *d, const int32_
   if (lb || lt) {
     Status h;
     CEL_TRY(read_status(st, &h, s));
+    turn.done();
     if (h.err) return status_error(h, fn);
     k_fill_i64<<<1, 64, 0, s>>>(&st->s0, 2, 0);  // s0, s1: the maxima, taken again below
     if (lb) {

@@ -4,6 +4,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <mutex>
 #include <vector>
 
 #include "cel.h"
@@ -347,6 +348,29 @@ class Scratch {
   int err_ = CEL_OK;
   char *base_ = nullptr;  // fixed range (second form), else null
   size_t cap_ = 0, off_ = 0;
+};
+
+// The device's turn of grids whose workgroups wait for each other (grid_sync).
+// Such a grid may need every CU to itself, and two of them on different
+// streams that each hold some of the CUs would wait for the rest until both
+// give up.  So one call at a time has them in flight on a device: take()
+// before the first launch, done() once the stream has been drained (the status
+// read that ends the stretch).  take() waits no longer than the barriers' own
+// waits last (a second or so: the holder's stream may be behind a caller's long
+// kernel) and returns false then, as the grid that could not be launched: the
+// caller takes its other method.
+class GridTurn {
+ public:
+  explicit GridTurn(hipStream_t s) : s_(s) {}
+  ~GridTurn();  // an error that left before the status read: drains the stream
+  GridTurn(const GridTurn &) = delete;
+  GridTurn &operator=(const GridTurn &) = delete;
+  bool take();  // true if it is held already
+  void done();
+
+ private:
+  hipStream_t s_;
+  std::timed_mutex *mu_ = nullptr;
 };
 
 // Launch-configuration helpers
@@ -750,7 +774,8 @@ int ms_ring(int32_t n, int32_t m, int32_t L, const int32_t *lp, const int32_t *g
 // grid cannot be launched (the caller runs the level sweep).
 int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
               const int32_t *aidx, const int64_t *wv, int kind, int64_t *out, int32_t *res,
-              const char *timer, class Scratch &sc, hipStream_t s, Status *st, bool *launched);
+              const char *timer, class Scratch &sc, hipStream_t s, Status *st, class GridTurn &turn,
+              bool *launched);
 // whether the calling thread's cel_topo_levels and cel_blevel calls try
 // policy iteration first (cel_policy_iteration)
 bool policy_iteration_on();
@@ -762,10 +787,10 @@ bool policy_iteration_packed();  // packed entries allowed (mode 1), else 16-byt
 // cluster starts from the DP's back pointers by doubling tables (flag[j] = 1
 // at every start, st->i0 = their number); *launched false: nothing queued
 int chain_marks(int32_t n, const int32_t *P, int32_t *flag, Scratch &sc, hipStream_t s, Status *st,
-                bool *launched);
+                GridTurn &turn, bool *launched);
 int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t *PO,
               const int64_t *cq, const int32_t *sptr, const int32_t *sidx, int32_t *P,
-              class Scratch &sc, hipStream_t s, Status *st, bool *launched);
+              class Scratch &sc, hipStream_t s, Status *st, GridTurn &turn, bool *launched);
 // ms_relax.hip: finish times of one placement by relaxation over the
 // cross-device edges (devp = devices by position).  Queues the preparation
 // and one persistent kernel on s and sets *launched; st->i3 = 1 once the
@@ -776,7 +801,7 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
 int ms_relax(const cel_graph *g, const cel_devices *d, int32_t L, const int32_t *order,
              const uint8_t *node_dev, const uint8_t *devp, int64_t *start, int64_t *finish,
              int64_t *makespan, int max_groups, class Scratch &sc, hipStream_t s, Status *st,
-             bool *launched);
+             GridTurn &turn, bool *launched);
 // makespan_model.hip: a heterogeneous descriptor's ranges, its slowest
 // multiplier, smallest bandwidth and largest latency; lead[g] = smallest
 // pos[v] over the members v of group g (INT32_MAX before)

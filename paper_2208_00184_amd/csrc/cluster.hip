@@ -1187,6 +1187,7 @@ extern "C" int cel_cluster(const cel_graph *g, const cel_devices *d, const int32
   CEL_TRY(exclusive_scan_i64(memp, PM, n, sc, s));
   CEL_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t) * (size_t)n, s));
   k_cluster_bounds<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, R, M, PM, lo, gend, st);
+  GridTurn turn(s);
   if (mode == CEL_CLUSTER_DP) {
     int32_t *pptr, *pidx, *P;
     CEL_TRY(sc.get(&pptr, (int64_t)n + 1));
@@ -1202,10 +1203,11 @@ extern "C" int cel_cluster(const cel_graph *g, const cel_devices *d, const int32
       CEL_TRY(sc.get(&sidx, g->m));
       CEL_TRY(relabel_csr(n, g->m, order, pos, g->out_ptr, g->out_idx, sptr, sidx, sc, s, st));
       bool launched = false;
-      CEL_TRY(dp_policy(n, g->m, R, lo, PO, cq, sptr, sidx, P, sc, s, st, &launched));
+      CEL_TRY(dp_policy(n, g->m, R, lo, PO, cq, sptr, sidx, P, sc, s, st, turn, &launched));
       if (launched) {
         Status h;
         CEL_TRY(read_status(st, &h, s));
+        turn.done();
         if (h.err) return status_error(h, fn);
         solved = h.i2 != 0;
         t_cl_info = {solved ? 0 : 1, h.i3};
@@ -1225,7 +1227,7 @@ extern "C" int cel_cluster(const cel_graph *g, const cel_devices *d, const int32
     else if (R <= 2048) launch_dp<32>(n, R, lo, pptr, pidx, cq, PO, P, st, s);
     else launch_dp<64>(n, R, lo, pptr, pidx, cq, PO, P, st, s);
     bool marked = false;
-    if (policy_iteration_on()) CEL_TRY(chain_marks(n, P, flag, sc, s, st, &marked));
+    if (policy_iteration_on()) CEL_TRY(chain_marks(n, P, flag, sc, s, st, turn, &marked));
     if (!marked) k_walk<true><<<1, kWalkB, 0, s>>>(n, P, flag, st);
   } else {
     k_walk<false><<<1, kWalkB, 0, s>>>(n, gend, flag, st);
@@ -1237,6 +1239,7 @@ extern "C" int cel_cluster(const cel_graph *g, const cel_devices *d, const int32
   CEL_HIP(hipGetLastError());
   Status h;
   CEL_TRY(read_status(st, &h, s));
+  turn.done();
   if (h.err) return status_error(h, fn);
   *n_clusters = h.i0;
   *cut_cost = h.s0;

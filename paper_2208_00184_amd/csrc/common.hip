@@ -1,5 +1,6 @@
 // Shared pieces of libcel: error state, scratch memory, input validation,
 // prefix scans, CSR relabelling into position space and a segmented sort.
+#include <chrono>
 #include <cstdarg>
 #include <cstring>
 #include <map>
@@ -161,6 +162,39 @@ int read_status(const Status *dst, Status *host, hipStream_t s) {
   CEL_HIP(hipMemcpyAsync(host, dst, sizeof(Status), hipMemcpyDeviceToHost, s));
   CEL_HIP(hipStreamSynchronize(s));
   return CEL_OK;
+}
+
+// ---------------------------------------------------- turn of the whole grids
+
+static std::mutex g_turn_mu;
+static std::map<int, std::timed_mutex *> g_turns;  // one a device, kept until the process ends
+constexpr auto kTurnWait = std::chrono::seconds(1);
+
+bool GridTurn::take() {
+  if (mu_) return true;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::timed_mutex *m;
+  {
+    std::lock_guard<std::mutex> lk(g_turn_mu);
+    std::timed_mutex *&t = g_turns[dev];
+    if (!t) t = new std::timed_mutex();
+    m = t;
+  }
+  if (!m->try_lock_for(kTurnWait)) return false;
+  mu_ = m;
+  return true;
+}
+
+void GridTurn::done() {
+  if (mu_) mu_->unlock();
+  mu_ = nullptr;
+}
+
+GridTurn::~GridTurn() {
+  if (!mu_) return;
+  (void)hipStreamSynchronize(s_);
+  done();
 }
 
 // ------------------------------------------------------------ side stream

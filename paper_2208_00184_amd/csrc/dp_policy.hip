@@ -722,7 +722,7 @@ std::map<int, int> g_cm_groups;  // the same for k_chain_marks
 
 int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t *PO,
               const int64_t *cq, const int32_t *sptr, const int32_t *sidx, int32_t *P,
-              Scratch &sc, hipStream_t s, Status *st, bool *launched) {
+              Scratch &sc, hipStream_t s, Status *st, GridTurn &turn, bool *launched) {
   *launched = false;
   if (n <= 0) return CEL_OK;
   int gmax = 0;
@@ -824,6 +824,7 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
     CEL_TRY(sc.get(&a.dfl, 2 * ((int64_t)n / 64 + 1)));
     a.bar = bar;
     a.st = st;
+    if (!turn.take()) return CEL_OK;
     {
       KTimer kt(s, "k_cluster_policy");
       if (T == 5) k_dp_tiles<5><<<G, kDpB, 0, s>>>(a);
@@ -863,6 +864,7 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
   CEL_TRY(sc.get(&a.e1, (int64_t)n + 1));
   a.bar = bar;
   a.st = st;
+  if (!turn.take()) return CEL_OK;
   {
     // at most one workgroup per CU, within the occupancy calculator's limit:
     // resident all at once on an idle GPU; the barriers' waits are bounded
@@ -875,7 +877,7 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
 }
 
 int chain_marks(int32_t n, const int32_t *P, int32_t *flag, Scratch &sc, hipStream_t s, Status *st,
-                bool *launched) {
+                GridTurn &turn, bool *launched) {
   *launched = false;
   if (n <= 0) return CEL_OK;
   int gmax = 0;
@@ -893,7 +895,7 @@ int chain_marks(int32_t n, const int32_t *P, int32_t *flag, Scratch &sc, hipStre
     }
     gmax = it->second;
   }
-  if (gmax < 1) return CEL_OK;
+  if (gmax < 1 || !turn.take()) return CEL_OK;
   const int64_t need = ((int64_t)n + 1 + kDpB - 1) / kDpB;
   const int G = (int)(need < gmax ? need : gmax);
   int32_t K = 2;  // 2^(K - 1) > n: enough levels for a chain through every position

@@ -475,12 +475,13 @@ int lp_groups(int *out) {
 
 int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
               const int32_t *aidx, const int64_t *wv, int kind, int64_t *out, int32_t *res,
-              const char *timer, Scratch &sc, hipStream_t s, Status *st, bool *launched) {
+              const char *timer, Scratch &sc, hipStream_t s, Status *st, GridTurn &turn,
+              bool *launched) {
   *launched = false;
   if (n <= 0) return CEL_OK;
   int gmax = 0;
   CEL_TRY(lp_groups(&gmax));
-  if (gmax < 1) return CEL_OK;
+  if (gmax < 1 || !turn.take()) return CEL_OK;
   const int G = (int)((int64_t)n + kLpB - 1) / kLpB < gmax ? (int)(((int64_t)n + kLpB - 1) / kLpB)
                                                           : gmax;
   // pointer chains are at most L nodes long (one per level)

@@ -930,12 +930,14 @@ static int makespan_impl(const char *fn, const cel_graph *g, const cel_devices *
     // rounds unless the placement changes device along most long paths.
     const Scratch::Mark mk = sc.mark();
     bool launched = false;
+    GridTurn turn(s);
     if (t_ms_relax > 0)
       CEL_TRY(ms_relax(g, d, L, order, node_dev, dev0, start, finish, makespan,
-                       t_ms_relax > 1 ? t_ms_relax : 0, sc, s, st, &launched));
+                       t_ms_relax > 1 ? t_ms_relax : 0, sc, s, st, turn, &launched));
     if (launched) {
       Status h;
       CEL_TRY(read_status(st, &h, s));
+      turn.done();
       if (h.err) return status_error(h, fn);
       t_ms_info = {0, h.i2};
       if (h.i3) return CEL_OK;

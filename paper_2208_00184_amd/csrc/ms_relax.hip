@@ -449,7 +449,7 @@ int rx_device(RxDev *out) {
 int ms_relax(const cel_graph *g, const cel_devices *d, int32_t L, const int32_t *order,
              const uint8_t *node_dev, const uint8_t *devp, int64_t *start, int64_t *finish,
              int64_t *makespan, int max_groups, Scratch &sc, hipStream_t s, Status *st,
-             bool *launched) {
+             GridTurn &turn, bool *launched) {
   *launched = false;
   const int32_t n = g->n, m = g->m, D = d->D;
   RxDev rd;
@@ -467,7 +467,7 @@ int ms_relax(const cel_graph *g, const cel_devices *d, int32_t L, const int32_t 
       G = (int)need;
     }
   }
-  if (ti < 0) return CEL_OK;  // too large for one co-resident grid
+  if (ti < 0 || !turn.take()) return CEL_OK;  // too large for one co-resident grid, or no turn
   // The grid is at most one workgroup per CU, within what the occupancy
   // calculator says fits: on an idle GPU every workgroup is resident at once,
   // which the grid barriers need.  Their waits are bounded (kGridSpin), so a

@@ -540,8 +540,9 @@ extern "C" int cel_topo_levels(const cel_graph *g, int32_t *level, int32_t *orde
     CEL_TRY(sc.get(&val, n));
     k_topo_wv<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, g->in_ptr, wv, st);
     bool launched = false;
+    GridTurn turn(s);
     CEL_TRY(lp_policy(n, g->m, n, policy_iteration_packed() ? topo_policy_cap(n) : kTopoPolicyIt, g->in_ptr, g->in_idx, wv, 2, val, &st->i2,
-                      "k_levels_policy", sc, s, st, &launched));
+                      "k_levels_policy", sc, s, st, turn, &launched));
     if (launched) {
       // order_id: the nodes sorted by (level, id), one segment, queued before
       // the status is read (one host round trip when the iteration
@@ -558,6 +559,7 @@ extern "C" int cel_topo_levels(const cel_graph *g, int32_t *level, int32_t *orde
       CEL_HIP(hipGetLastError());
       Status h;
       CEL_TRY(read_status(st, &h, s));
+      turn.done();
       if (h.err) return status_error(h, "cel_topo_levels");
       t_topo_info = {h.i2 ? 0 : 1, h.i3};
       if (h.i2) {
