@@ -370,7 +370,7 @@ int cel_topo_levels_info(int32_t *info);
  * pointers (graphs of 3,072 nodes and more), exact after info[1]
  * iterations; 1: by the blocked sequential DP (after info[1] iterations that
  * did not converge within their budget, or 0 when policy iteration was not
- * tried).
+ * tried or other work kept its workgroups off the GPU).
  * Outputs: info [2] (host).
  * Errors: CEL_E_ARG (NULL argument). */
 int cel_cluster_info(int32_t *info);
@@ -380,8 +380,10 @@ int cel_cluster_info(int32_t *info);
  * level sweeps and the blocked DP directly; 1 (the default) tries policy
  * iteration first, with packed 64-bit entries and asynchronous pointer
  * jumping where the values fit; 2 tries policy iteration first with 16-byte
- * entries and synchronous rounds everywhere.  Every mode gives the same
- * results.  Returns the previous mode (CEL_E_ARG for a negative mode). */
+ * entries and synchronous rounds everywhere; 3 is as 1, but the clustering
+ * DP's iteration gives up at its first barrier, as if other work kept its
+ * workgroups off the GPU (for tests).  Every mode gives the same results.
+ * Returns the previous mode (CEL_E_ARG for a negative mode). */
 int cel_policy_iteration(int mode);
 
 /* Diagnostics: which K = 1 path the calling thread's cel_makespan and

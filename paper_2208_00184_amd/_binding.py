@@ -174,7 +174,8 @@ def policy_iteration(mode: int) -> int:
     0 = Kahn's kernel, the level sweeps and the blocked DP, 1 = policy
     iteration first (default; packed entries and asynchronous pointer jumping
     where the values fit), 2 = policy iteration first with 16-byte entries and
-    synchronous rounds; returns the previous mode."""
+    synchronous rounds, 3 = as 1, but the clustering DP's iteration gives up at
+    its first barrier (for tests); returns the previous mode."""
     r = lib().cel_policy_iteration(int(mode))
     if r < 0:
         _check(r)

@@ -88,7 +88,8 @@ static thread_local int t_lp_mode = 1;
 
 namespace cel {
 bool policy_iteration_on() { return t_lp_mode > 0; }
-bool policy_iteration_packed() { return t_lp_mode == 1; }
+bool policy_iteration_packed() { return t_lp_mode == 1 || t_lp_mode == 3; }
+bool policy_iteration_gives_up() { return t_lp_mode == 3; }
 }  // namespace cel
 
 extern "C" int cel_blevel_info(int32_t *info) {

@@ -780,6 +780,7 @@ int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
 // policy iteration first (cel_policy_iteration)
 bool policy_iteration_on();
 bool policy_iteration_packed();  // packed entries allowed (mode 1), else 16-byte rounds
+bool policy_iteration_gives_up();  // the clustering DP's grid barriers give up at once (mode 3)
 // dp_policy.hip: the clustering DP's back pointers P[1..n] (smallest
 // minimising i) and st->s0 = S(n) by policy iteration, given lo, PO, the comm
 // by position and the successors in positions (sptr / sidx).  st->i2 = 1 once

@@ -1208,9 +1208,13 @@ extern "C" int cel_cluster(const cel_graph *g, const cel_devices *d, const int32
         Status h;
         CEL_TRY(read_status(st, &h, s));
         turn.done();
-        if (h.err) return status_error(h, fn);
-        solved = h.i2 != 0;
-        t_cl_info = {solved ? 0 : 1, h.i3};
+        if (h.err & ~(uint32_t)EB_WAIT) return status_error(h, fn);
+        if (h.err) {  // other work kept some of its workgroups off the GPU: the blocked DP
+          k_fill_i32<<<1, 64, 0, s>>>((int32_t *)&st->err, 1, 0);
+        } else {
+          solved = h.i2 != 0;
+          t_cl_info = {solved ? 0 : 1, h.i3};
+        }
       }
     }
     bool blocked = false;

@@ -761,6 +761,8 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
   CEL_TRY(sc.get(&cost, (int64_t)n + 1));
   k_fill_i32<<<grid_for((int64_t)n + 2 + gmax, 256, 4096), 256, 0, s>>>(ncnt, (int64_t)n + 2 + gmax,
                                                                       0);
+  // (bar[1]: the barriers' abort flag)
+  if (policy_iteration_gives_up()) k_fill_i32<<<1, 64, 0, s>>>(bar + 1, 1, 1);
   k_dpn_count<<<edge_blocks(m), 256, 0, s>>>(n, m, R, sptr, sidx, ncnt, st);
   CEL_TRY(exclusive_scan_i32(ncnt, nptr, n, sc, s));
   k_dpn_fill<<<edge_blocks(m), 256, 0, s>>>(n, m, R, sptr, sidx, nptr, ncnt, noff, st);

@@ -95,3 +95,17 @@ def test_many_count_tables():
     dst = np.concatenate([rng.integers(701, 760, 70000), rng.integers(702, 800, 3000), np.arange(1, n)])
     wl = from_edges(n, np.stack([src, dst], 1), rng.integers(0, 50, n), rng.integers(0, 300, n), 2, [10 ** 12] * 2, 7, 3)
     check(wl, np.arange(n), 90, 10 ** 12)
+
+
+@pytest.mark.parametrize("n", [16384, 70001])
+def test_workgroups_kept_off_the_gpu(n):
+    """The iteration's barriers give up (forced from the host: every workgroup
+    ends at its first wait): the blocked DP gives the result."""
+    wl = near_dag(n, 5, 90, 3)
+    was = cel.policy_iteration(3)
+    try:
+        check(wl, np.arange(n), 64, -1, policy=False)
+        assert cel.cluster_info() == (1, 0)
+    finally:
+        cel.policy_iteration(was)
+    check(wl, np.arange(n), 64, -1)
