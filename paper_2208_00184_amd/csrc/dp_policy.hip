@@ -770,6 +770,7 @@ int dp_policy(int32_t n, int32_t m, int32_t R, const int32_t *lo, const int64_t 
   CEL_TRY(exclusive_scan_i32(hflag, hoff, n, sc, s, &st->i1));
   Status hs;
   CEL_TRY(read_status(st, &hs, s));
+  if (hs.err) return CEL_OK;  // the counts were not written; the caller reports it
   const int32_t H = hs.i1;  // positions with more than four offsets below R
   const int64_t total = hs.s1;
   if ((int64_t)H * (R + 1) * 4 > (int64_t(1) << 30)) return CEL_OK;  // tables too large: blocked DP

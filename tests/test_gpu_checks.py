@@ -108,3 +108,26 @@ def test_many_sorted_levels(L):
     bl, _, prio, _ = cel.blevel(g, d, glev, glp, goid, gL)
     ref = O.blevel(wl, lev, oid)
     assert np.array_equal(bl.cpu().numpy(), ref[0]) and np.array_equal(prio.cpu().numpy(), ref[2])
+
+
+def test_refused_order_takes_no_table_space():
+    """A clustering call whose order is refused leaves its counts of positions
+    with many successors unwritten: what an earlier call on the stream left in
+    that scratch must not size the tables."""
+    n, R = 4096, 63
+    v = np.arange(1, n)
+    wl = from_edges(n, np.stack([np.zeros_like(v), v], 1), np.where(np.arange(n) == 0, 2000, 0), np.zeros(n), 2,
+                    [10 ** 15] * 2, 3, 0)
+    g, d = up(wl)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        lev, oid, lp, L = cel.topo_levels(g)
+        # every finish time is 2,000: summed as int32 over n words, 4.1 million positions, 1.05 GB of tables
+        for _ in range(2):  # the second in one block of scratch
+            ms, _, _ = cel.makespan(g, d, oid, lev, lp, L, torch.zeros((64, n), dtype=torch.uint8, device=DEV))
+        assert (ms == 2000).all()
+        dup = np.arange(n)
+        dup[-1] = 0
+        free = torch.cuda.mem_get_info()[0]
+        assert code(lambda: cel.cluster(g, d, tt(dup), R, -1)) == ORDER
+        assert free - torch.cuda.mem_get_info()[0] < 1 << 28
