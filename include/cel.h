@@ -345,6 +345,17 @@ int cel_kernel_stats(char *buf, int buflen, int reset);
  * Errors: CEL_E_ARG (NULL argument). */
 int cel_makespan_info(int32_t *path, int32_t *rounds);
 
+/* Diagnostics: whether the calling thread's last cel_makespan,
+ * cel_makespan_noalloc or cel_makespan_model call took blocks of tasks (device
+ * models without insertion, batches over narrow levels).  info[0] = 0: the
+ * blocks gave the result; 1: another method did.  info[1], info[2]: the
+ * iterations and blocks of the placement that took most of each (with info[0]
+ * = 1: of a try whose values did not fit or that outran its budget, or 0 when
+ * blocks were not tried).
+ * Outputs: info [3] (host).
+ * Errors: CEL_E_ARG (NULL argument). */
+int cel_makespan_blocks_info(int32_t *info);
+
 /* Diagnostics: how the calling thread's last cel_blevel call found its
  * longest paths.  info[0] = 0: the b-level by policy iteration (each node
  * follows one successor; pointer jumping sums the chains; nodes switch to a

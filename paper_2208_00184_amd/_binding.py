@@ -21,7 +21,7 @@ COMM_OFF = 1
 CLUSTER_DP, CLUSTER_GREEDY = 0, 1
 
 EXPORTS = ("cel_topo_levels", "cel_blevel", "cel_cpd_order", "cel_dfs_order", "cel_cluster", "cel_place", "cel_place_ext", "cel_makespan", "cel_makespan_noalloc",
-           "cel_makespan_info", "cel_makespan_relax", "cel_blevel_info", "cel_policy_iteration",
+           "cel_makespan_info", "cel_makespan_blocks_info", "cel_makespan_relax", "cel_blevel_info", "cel_policy_iteration",
            "cel_topo_levels_info", "cel_cluster_info",
            "cel_order_place", "cel_comm_sums", "cel_makespan_model", "cel_colocate", "cel_step_latency", "cel_timing", "cel_kernel_stats", "cel_last_error", "cel_version")
 
@@ -92,6 +92,8 @@ def lib() -> C.CDLL:
         L.cel_kernel_stats.restype = C.c_int
         L.cel_makespan_info.argtypes = [C.POINTER(i32), C.POINTER(i32)]
         L.cel_makespan_info.restype = C.c_int
+        L.cel_makespan_blocks_info.argtypes = [C.POINTER(i32)]
+        L.cel_makespan_blocks_info.restype = C.c_int
         L.cel_makespan_relax.argtypes = [C.c_int]
         L.cel_makespan_relax.restype = C.c_int
         L.cel_blevel_info.argtypes = [C.POINTER(i32)]
@@ -129,6 +131,16 @@ def makespan_info() -> tuple:
     path, rounds = C.c_int32(0), C.c_int32(0)
     _check(lib().cel_makespan_info(C.byref(path), C.byref(rounds)))
     return path.value, rounds.value
+
+
+def makespan_blocks_info() -> tuple:
+    """(path, iterations, blocks) of the calling thread's last makespan or
+    makespan_model call: path 0 = blocks of tasks gave the result, 1 = another
+    method did (iterations and blocks of a try that was given up, or 0); of the
+    placement that took most of each."""
+    info = (C.c_int32 * 3)()
+    _check(lib().cel_makespan_blocks_info(info))
+    return info[0], info[1], info[2]
 
 
 def makespan_relax(mode: int) -> int:

@@ -747,6 +747,9 @@ struct MsBlocks {
   const char *timer;
 };
 int ms_blocks(const MsBlocks &b, class Scratch &sc, hipStream_t s, Status *st);
+// what cel_makespan_blocks_info reports: the status after ms_blocks (st->i2,
+// st->i3: most iterations and blocks of a placement), or NULL: not tried
+void ms_blocks_info(const Status *h);
 // makespan_model.hip: first 4 inputs of each position (-1 past the row's end)
 __global__ void k_mm_ipre(int32_t n, const int32_t *iptr, const int32_t *iidx, int4 *ipre,
                           const Status *st);

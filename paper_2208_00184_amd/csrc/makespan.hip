@@ -898,6 +898,7 @@ static int makespan_impl(const char *fn, const cel_graph *g, const cel_devices *
                          int32_t L, int32_t K, const uint8_t *node_dev, int64_t *start,
                          int64_t *finish, int64_t *makespan, Scratch &sc, hipStream_t s) {
   const int32_t n = g->n;
+  ms_blocks_info(nullptr);
   Status *st;
   int32_t *pos, *pptr, *pidx;
   int64_t *wp, *cq, *finp;
@@ -1033,6 +1034,7 @@ static int makespan_impl(const char *fn, const cel_graph *g, const cel_devices *
         Status hb;
         CEL_TRY(read_status(st, &hb, s));
         if (hb.err) return status_error(hb, fn);
+        ms_blocks_info(&hb);
         if (!hb.i1) return CEL_OK;
         sc.release(mk);
       }

@@ -1075,6 +1075,7 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
       return set_error(CEL_E_OVERFLOW, "%s: times could reach 2^62", fn);
     worst_total = (int64_t)tot;
   }
+  ms_blocks_info(nullptr);
   Scratch sc(s);
   Status *st;
   CEL_TRY(sc.get(&st, 1));
@@ -1212,6 +1213,7 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
     Status hb;
     CEL_TRY(read_status(st, &hb, s));
     if (hb.err) return status_error(hb, fn);
+    ms_blocks_info(&hb);
     if (!hb.i1) return CEL_OK;
     sc.release(mk);
   }

@@ -291,7 +291,7 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
   const uint8_t *dev = a.devp + kn;
   int64_t *val = a.val + t0;
   int64_t span = 0;
-  int32_t its = 0, nt = 0;
+  int32_t its = 0, nblk = 0, nt = 0;  // nblk: blocks that ended
   int32_t pp0 = 0;  // the previous block's first task
   if (tid == 0) {
     s_ent[0][kBkB] = s_ent[1][kBkB] = kEnd;
@@ -562,7 +562,11 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
       lds_barrier();
       if (!s_chg[i]) break;
       if (its > a.budget) {  // uniform: the caller runs the other method
-        if (tid == 0) atomicOr(&st->i1, 1);
+        if (tid == 0) {
+          atomicOr(&st->i1, 1);
+          atomicMax(&st->i2, its);
+          atomicMax(&st->i3, nblk);
+        }
         return;
       }
     }
@@ -576,6 +580,7 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
       if (inf[u] & kBkLast1) s_free[kk[u] & 255u] = v[u];
       if (XFER && (inf[u] & kBkLast2)) s_free[kk[u] >> 8] = v[u];
     }
+    nblk++;
     pp0 = p0;
     p0 += nt;
     par ^= 1;
@@ -589,10 +594,23 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
   if (tid == 0) {
     for (int i = 1; i < kBkT / 64; i++) span = max_nonneg(span, s_red[i]);
     a.makespan[blockIdx.x] = span;
+    atomicMax(&st->i2, its);
+    atomicMax(&st->i3, nblk);
   }
 }
 
 // ------------------------------------------------------------------- host
+
+namespace {
+struct BkInfo {
+  int32_t path, iters, blocks;
+};
+thread_local BkInfo t_bk_info{1, 0, 0};
+}  // namespace
+
+void ms_blocks_info(const Status *h) {
+  t_bk_info = h ? BkInfo{h->i1 ? 1 : 0, h->i2, h->i3} : BkInfo{1, 0, 0};
+}
 
 int ms_blocks(const MsBlocks &b, Scratch &sc, hipStream_t s, Status *st) {
   const int64_t Kn = (int64_t)b.K * b.n;
@@ -662,3 +680,12 @@ int ms_blocks(const MsBlocks &b, Scratch &sc, hipStream_t s, Status *st) {
 }
 
 }  // namespace cel
+
+extern "C" int cel_makespan_blocks_info(int32_t *info) {
+  using namespace cel;
+  if (!info) return set_error(CEL_E_ARG, "cel_makespan_blocks_info: NULL argument");
+  info[0] = t_bk_info.path;
+  info[1] = t_bk_info.iters;
+  info[2] = t_bk_info.blocks;
+  return CEL_OK;
+}

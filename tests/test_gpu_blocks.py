@@ -54,13 +54,21 @@ def placements(n, D, K, seed):
     return P
 
 
-def check_model(wl, P, model, **het):
+def took_blocks(yes):
+    path, its, blocks = cel.makespan_blocks_info()
+    print(f"[blocks] path {path}, {its} iterations, {blocks} blocks", flush=True)
+    assert yes is None or path == (0 if yes else 1)
+    return its, blocks
+
+
+def check_model(wl, P, model, blocks=True, **het):
     g, d = cel.Graph.from_arrays(wl, DEV), cel.Devices.from_arrays(wl)
     order = np.arange(wl.n)
     ms, st, fi = cel.makespan_model(g, d, tt(order, np.int32), tt(P, np.uint8), model, want_times=True, **het)
     rm, rs, rf = O.makespan_model(wl, order, P, model, **het)
     assert np.array_equal(ms.cpu().numpy(), rm), model
     assert np.array_equal(fi.cpu().numpy(), rf) and np.array_equal(st.cpu().numpy(), rs), model
+    return took_blocks(blocks)
 
 
 def hetero(D, seed):
@@ -75,8 +83,8 @@ def test_models(n, model):
     """FIFO devices take the blocks from 4,096 nodes on, transfers from 1,024."""
     for D in (2, 16, 64):
         P = placements(n, D, 4, 3)
-        check_model(dag(n, D, 3), P, model)
-        check_model(dag(n, D, 3), P[:2], model, **hetero(D, 4))
+        check_model(dag(n, D, 3), P, model, blocks=model != 0 or n >= 4096)
+        check_model(dag(n, D, 3), P[:2], model, blocks=model != 0 or n >= 4096, **hetero(D, 4))
 
 
 def test_one_device_and_tmul_only():
@@ -104,15 +112,15 @@ def test_listed_inputs_do_not_fit():
     wl = from_edges(wl.n, np.stack([src, dst], 1), wl.w, wl.ob, 3, [10 ** 15] * 3, 7, 3)
     P = placements(4500, 3, 3, 8)
     for model in (0, cel.MODEL_COMM_TASKS, cel.MODEL_COMM_BLOCK):
-        check_model(wl, P[:2], model)
+        check_model(wl, P[:2], model, blocks=None)
 
 
 def test_values_past_the_packed_words():
     wl = dag(2500, 4, 10, ob_max=1 << 40, w_max=1 << 45)
     P = placements(2500, 4, 3, 10)
     for model in (0, cel.MODEL_COMM_TASKS, cel.MODEL_COMM_BLOCK):
-        check_model(wl, P[:2], model)
-        check_model(wl, P[:1], model, **hetero(4, 11))
+        check_model(wl, P[:2], model, blocks=False)
+        check_model(wl, P[:1], model, blocks=False, **hetero(4, 11))
 
 
 def test_alternating_channels():
@@ -125,7 +133,7 @@ def test_alternating_channels():
         check_model(wl, P, model)
 
 
-def check_batch(wl, P, seed=0):
+def check_batch(wl, P, seed=0, blocks=True):
     """cel.makespan of a batch, with and without its own allocations, in level
     order with the ids shuffled inside each level."""
     lev, _, lp, L = O.topo_levels(wl)
@@ -136,6 +144,7 @@ def check_batch(wl, P, seed=0):
     for fixed in (False, True):
         ms, st, fi = cel.makespan(g, d, *args, want_times=True, noalloc=fixed)
         assert np.array_equal(ms.cpu().numpy(), rm), (wl.n, L, fixed)
+        took_blocks(blocks)
         assert np.array_equal(fi.cpu().numpy(), rf) and np.array_equal(st.cpu().numpy(), rs), (wl.n, L, fixed)
         ms, st, fi = cel.makespan(g, d, *args, noalloc=fixed)
         assert np.array_equal(ms.cpu().numpy(), rm) and st is None and fi is None
@@ -145,7 +154,7 @@ def check_batch(wl, P, seed=0):
 @pytest.mark.parametrize("n", [1023, 1024, 1025, 2047, 2048, 2049, 4097, 9000])
 @pytest.mark.parametrize("D", [1, 2, 16, 64, 65, 255])
 def test_batches_of_placements(n, D):
-    L = check_batch(dag(n, D, 12, reach=60), placements(n, D, 5, 12), n)
+    L = check_batch(dag(n, D, 12, reach=60), placements(n, D, 5, 12), n, blocks=n >= 1024)
     assert n <= 48 * L  # narrow enough for the blocks (from 1,024 nodes on)
 
 
@@ -157,13 +166,13 @@ def test_batches_by_level_width(width):
     rng = np.random.default_rng(width)
     e = np.concatenate([np.stack([(v // width - 1) * width + rng.integers(0, width, v.size), v], 1) for _ in range(2)])
     wl = from_edges(n, e, rng.integers(0, 60, n), rng.integers(0, 400, n), 8, [10 ** 15] * 8, 7, 3)
-    assert check_batch(wl, placements(n, 8, 6, 13)) == 40
+    assert check_batch(wl, placements(n, 8, 6, 13), blocks=width <= 48) == 40
 
 
 def test_batches_at_the_limits():
     """Values past the packed words (the ring runs); hubs whose inputs do not
     fit beside their block; more scattered placements than CUs."""
-    check_batch(dag(2500, 4, 14, ob_max=1 << 40, w_max=1 << 45, reach=60), placements(2500, 4, 4, 14))
+    check_batch(dag(2500, 4, 14, ob_max=1 << 40, w_max=1 << 45, reach=60), placements(2500, 4, 4, 14), blocks=False)
     check_batch(dag(9000, 6, 15, fan=40, reach=90, hubs=((4000, 3000), (8191, 17000))), placements(9000, 6, 4, 15))
     n, rng = 3000, np.random.default_rng(16)
     L = check_batch(dag(n, 3, 16, reach=20, ob_max=4000, w_max=3), rng.integers(0, 3, (300, n)).astype(np.uint8))
