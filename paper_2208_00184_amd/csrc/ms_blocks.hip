@@ -33,8 +33,10 @@
 // 0.40; FIFO devices on inception-600 10.0 -> 0.44; transfers on the compute
 // queues there 15.2 -> 0.55.
 //
-// A block reserves list space in LDS for tasks of more than four inputs; where
-// it does not suffice the block is taken again with half the tasks.  A call
+// A block reserves list space in LDS for tasks of more than four inputs (of a
+// long row for as many as the block can hold); where it does not suffice the
+// block is taken again with half the tasks, and the next one with twice as many.
+// A call
 // whose values reach 2^47 (the packed words hold 48 bits), or that needs more
 // iterations than the other method would cost, raises st->i1 and writes no
 // result: the caller runs the other method.
@@ -443,9 +445,11 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
         const int l = __builtin_ctzll(hv);
         const int32_t ph = __builtin_amdgcn_readlane(hp, l), dh = __builtin_amdgcn_readlane(d, l);
         const int32_t e0 = a.iptr[ph], e1 = a.iptr[ph + 1];
-        int32_t o = 0, m = 0;
+        // at most nt - 1 of the inputs lie in the block, unless edges are parallel
+        int32_t o = 0, m = 0, room = 0;
         if (nt > 1) {
-          if (lane == l) o = atomicAdd(&s_ovn, e1 - e0);
+          room = e1 - e0 < nt ? e1 - e0 : nt;
+          if (lane == l) o = atomicAdd(&s_ovn, room);
           o = __builtin_amdgcn_readlane(o, l);
         }
         int64_t b = 0;
@@ -453,10 +457,11 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
           uint32_t s = kEnd;
           if (e + lane < e1) s = input(XFER ? xtask(a.iidx[e + lane], dh) : a.iidx[e + lane], dh, b);
           const uint64_t in = __ballot(s != kEnd);
-          const int32_t at = o + m + __popcll(in & ((1ull << lane) - 1));
-          if (s != kEnd && at < kBkOv) s_ov[at] = (uint16_t)s;
+          const int32_t at = m + __popcll(in & ((1ull << lane) - 1));
+          if (s != kEnd && at < room && o + at < kBkOv) s_ov[o + at] = (uint16_t)s;
           m += __popcll(in);
         }
+        if (m > room && lane == l) atomicAdd(&s_ovn, kBkOv + 1);
         for (int x = 32; x > 0; x >>= 1) b = max_nonneg(b, (int64_t)__shfl_xor((long long)b, x));
         if (lane == l) {
           base[u] = max_nonneg(base[u], b);
@@ -468,7 +473,8 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
     // behind this barrier: the next block reads them from memory.
     store_barrier();
     if (s_ovn > kBkOv) {  // too many listed inputs: half the tasks (nt = 1 lists none)
-      lim = nt / 2 > 0 ? nt / 2 : 1;
+      lim = nt / 2;
+      its++;          // about as long
       lds_barrier();  // every wave has read s_ovn before it is cleared
       continue;
     }
@@ -584,9 +590,17 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
     pp0 = p0;
     p0 += nt;
     par ^= 1;
-    if ((p0 & (kBkB - 1)) == 0) lim = kBkB;
+    lim = 2 * lim < kBkB ? 2 * lim : kBkB;
     lds_barrier();
     if (tid == 0) s_chg[0] = 0;  // the next block's first flag, read behind two more barriers
+    if (its > a.budget && p0 < N) {  // as above, whatever the block needed
+      if (tid == 0) {
+        atomicOr(&st->i1, 1);
+        atomicMax(&st->i2, its);
+        atomicMax(&st->i3, nblk);
+      }
+      return;
+    }
   }
   for (int o = 32; o > 0; o >>= 1) span = max_nonneg(span, (int64_t)__shfl_xor((long long)span, o));
   if (lane == 0) s_red[wave] = span;

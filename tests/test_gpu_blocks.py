@@ -104,7 +104,7 @@ def test_long_rows():
 
 def test_listed_inputs_do_not_fit():
     """A node of 20,000 parallel in-edges from its block: blocks are halved
-    down to that node alone."""
+    until few of its sources are beside it, and grow again behind it."""
     wl = dag(4500, 3, 8)
     rng = np.random.default_rng(9)
     src = np.concatenate([np.repeat(np.arange(wl.n), np.diff(wl.out_ptr)), rng.integers(3000, 3090, 20000)])
@@ -112,7 +112,26 @@ def test_listed_inputs_do_not_fit():
     wl = from_edges(wl.n, np.stack([src, dst], 1), wl.w, wl.ob, 3, [10 ** 15] * 3, 7, 3)
     P = placements(4500, 3, 3, 8)
     for model in (0, cel.MODEL_COMM_TASKS, cel.MODEL_COMM_BLOCK):
-        check_model(wl, P[:2], model, blocks=None)
+        its, blocks = check_model(wl, P[:2], model)
+        assert blocks <= 24  # 3 chunks of nodes alone, 5 with transfers
+
+
+def test_rows_longer_than_the_list():
+    """Nodes fed by every node before them, 17,000 to 19,999 inputs, two in one
+    block: only the inputs beside them are listed, so no block is halved."""
+    n = 20000
+    wl = dag(n, 6, 17, reach=60)
+    e = [np.stack([np.repeat(np.arange(n), np.diff(wl.out_ptr)), wl.out_idx], 1)]
+    e += [np.stack([np.arange(v), np.full(v, v)], 1) for v in (17000, 17100, n - 1)]
+    wl = from_edges(n, np.concatenate(e), wl.w, wl.ob, 6, [10 ** 15] * 6, 7, 3)
+    P = placements(n, 6, 4, 17)
+    for model in (0, cel.MODEL_COMM_TASKS, cel.MODEL_COMM_BLOCK):
+        its, blocks = check_model(wl, P[:2], model)
+        assert blocks <= (10 if model == 0 else 60)  # tasks: a transfer for every device a node feeds
+    its, blocks = check_model(wl, P[:1], 0, **hetero(6, 7))
+    assert blocks == 10
+    check_batch(wl, P)
+    assert cel.makespan_blocks_info()[2] == 10
 
 
 def test_values_past_the_packed_words():
