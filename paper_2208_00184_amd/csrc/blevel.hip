@@ -151,10 +151,10 @@ extern "C" int cel_blevel(const cel_graph *g, const cel_devices *d, const int32_
   bool lb = false, lt = false;
   GridTurn turn(s);
   if (policy_iteration_on()) {
-    CEL_TRY(lp_policy(n, g->m, L, 0, sptr, sidx, wv, 0, blp, &st->i0, "k_blevel_policy", sc, s,
+    CEL_TRY(lp_policy(n, g->m, L, sptr, sidx, wv, 0, blp, &st->i0, "k_blevel_policy", sc, s,
                       st, turn, &lb));
     if (tlp)
-      CEL_TRY(lp_policy(n, g->m, L, 0, pptr, pidx, wv, 1, tlp, &st->i2, "k_tlevel_policy", sc, s,
+      CEL_TRY(lp_policy(n, g->m, L, pptr, pidx, wv, 1, tlp, &st->i2, "k_tlevel_policy", sc, s,
                         st, turn, &lt));
   }
   bool sweep_b = true, sweep_t = tlp != nullptr;

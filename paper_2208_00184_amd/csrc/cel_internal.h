@@ -775,8 +775,8 @@ int ms_ring(int32_t n, int32_t m, int32_t L, const int32_t *lp, const int32_t *g
 // many as are cheaper than a level sweep of L levels).  res[0] = 1 once
 // converged (out written), res[1] = iterations; *launched false when the
 // grid cannot be launched (the caller runs the level sweep).
-int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
-              const int32_t *aidx, const int64_t *wv, int kind, int64_t *out, int32_t *res,
+int lp_policy(int32_t n, int32_t m, int32_t L, const int32_t *aptr, const int32_t *aidx,
+              const int64_t *wv, int kind, int64_t *out, int32_t *res,
               const char *timer, class Scratch &sc, hipStream_t s, Status *st, class GridTurn &turn,
               bool *launched);
 // whether the calling thread's cel_topo_levels and cel_blevel calls try

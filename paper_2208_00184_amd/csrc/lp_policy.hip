@@ -34,7 +34,10 @@ constexpr int kLpU = 4;           // nodes per thread with loads in flight toget
 
 
 struct LpArgs {
-  int32_t n, cap, max_rounds;
+  int32_t n, max_rounds;
+  int32_t cap;                    // iterations of 16-byte entries allowed
+  int32_t few, less;              // packed: fewer than `few` allowed are taken as `less`
+  float alt_us, alt_chunk_us;     // what the other method takes, and per chunk of a long list
   int32_t packed;                 // packed entries allowed where the values fit
   const int32_t *aptr, *aidx;     // adjacency (positions)
   const int64_t *wv;              // [n]
@@ -62,6 +65,8 @@ __device__ inline bool lp_better(int64_t v, int32_t q, int64_t bv, int32_t bq) {
 }
 
 constexpr int32_t kLpLong = -2;
+constexpr int32_t kLpKahnIt = 12;   // iterations tried before Kahn's kernel in any case
+constexpr int32_t kLpWide = 16384;  // edges of a level that the sweep gives to the whole GPU
 
 // the barrier's and the counter's words, and the result's two
 __global__ void k_lp_init(int32_t *bar, int32_t nw, int32_t *res) {
@@ -113,7 +118,7 @@ __global__ void k_lp_lists(int32_t n, const int32_t *aptr, const int32_t *aidx, 
 // KIND: 0 the b-level, 1 the t-level (out = val - wv), 2 the levels of Kahn's
 // ordering; a template parameter so that profiles tell the three apart
 template <int KIND, bool PK>
-__device__ inline void lp_run(const LpArgs &a, int32_t *s_okp, int32_t *s_bitp) {
+__device__ inline void lp_run(const LpArgs &a, int32_t *s_okp, int32_t *s_bitp, const int32_t *s_cap) {
   int32_t &s_ok = *s_okp, &s_bit = *s_bitp;
   Status *st = a.st;
   const int32_t n = a.n;
@@ -136,7 +141,7 @@ __device__ inline void lp_run(const LpArgs &a, int32_t *s_okp, int32_t *s_bitp) 
   LpE *cur = a.e0, *oth = a.e1;
   int32_t it = 0;
   bool done = false;
-  for (; it < a.cap; it++) {
+  for (; it < *s_cap; it++) {  // (in LDS: the loop has no register to spare)
     // ---- improvement: the best neighbour under the current values
     // chunks of long lists, one wave each
     const int64_t wid = gid >> 6, nw = gsz >> 6;
@@ -443,12 +448,20 @@ __device__ inline void lp_run(const LpArgs &a, int32_t *s_okp, int32_t *s_bitp) 
 // EB_CYCLE.
 template <int KIND>
 __global__ void __launch_bounds__(kLpB) k_lp_policy(LpArgs a) {
-  __shared__ int32_t s_ok, s_bit;
+  __shared__ int32_t s_ok, s_bit, s_cap;
   if (failed(a.st)) return;
-  if (a.packed && a.n < (int32_t)kPkEnd && (KIND == 2 || a.st->total < (uint64_t(1) << 40)))
-    lp_run<KIND, true>(a, &s_ok, &s_bit);
-  else
-    lp_run<KIND, false>(a, &s_ok, &s_bit);
+  const bool pk = a.packed && a.n < (int32_t)kPkEnd && (KIND == 2 || a.st->total < (uint64_t(1) << 40));
+  if (threadIdx.x == 0) {
+    s_cap = a.cap;
+    if (pk) {  // by what an iteration costs with this many chunks (lp_policy)
+      const float H = (float)*a.hcount;
+      const float it_us = 25.0f + 1.2e-4f * (float)a.n + 5.0f / (kLpB / 64) * H / (float)gridDim.x;
+      const float c = (a.alt_us + a.alt_chunk_us * H) / it_us;
+      s_cap = c < (float)a.few ? a.less : (int32_t)c;
+    }
+  }
+  if (pk) lp_run<KIND, true>(a, &s_ok, &s_bit, &s_cap);
+  else lp_run<KIND, false>(a, &s_ok, &s_bit, &s_cap);
 }
 
 // ------------------------------------------------------------------- host
@@ -473,8 +486,8 @@ int lp_groups(int *out) {
 }
 }  // namespace
 
-int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
-              const int32_t *aidx, const int64_t *wv, int kind, int64_t *out, int32_t *res,
+int lp_policy(int32_t n, int32_t m, int32_t L, const int32_t *aptr, const int32_t *aidx,
+              const int64_t *wv, int kind, int64_t *out, int32_t *res,
               const char *timer, Scratch &sc, hipStream_t s, Status *st, GridTurn &turn,
               bool *launched) {
   *launched = false;
@@ -487,19 +500,38 @@ int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
   // pointer chains are at most L nodes long (one per level)
   int32_t max_rounds = 2;
   while ((int64_t(1) << (max_rounds - 2)) < L) max_rounds++;
-  // Iterations allowed (cap <= 0: before the level sweep is cheaper).  Packed
-  // entries: 37 us an iteration at 200k nodes, 147 at 1.07M.  16-byte entries:
-  // about max_rounds barriers and passes over 48 bytes per node, plus one pass
-  // over the neighbour lists.  The sweep with its preparation: 0.6 us per level
-  // and 5 ns per node (wide levels) after 0.5 ms; layered graphs of 200k nodes
-  // converge after 19 to 22 iterations, the transformer graphs after 6 to 12.
-  if (cap <= 0) {
-    const double it_us = policy_iteration_packed()
-                             ? 25.0 + 1.2e-4 * n
-                             : max_rounds * (5.0 + 48.0 * n / 4.0e6) + 12.0 * m / 4.0e6;
-    const double sweep_us = 500.0 + 0.6 * L + (policy_iteration_packed() ? 5e-3 * n : 0.0);
-    cap = (int32_t)(sweep_us / it_us);
-    if (cap < 2) cap = 2;
+  // Iterations allowed: what the level-synchronous method takes, over what an
+  // iteration takes.  Packed entries: 25 us and 0.12 ns a node, and 5 us for
+  // each chunk of a list of more than kLpLight entries that a wave has to read
+  // (graphs of 20k to 1.07M nodes, 2 to 100 edges a node: 17 to 39, 87 to 147 us
+  // without such lists at 200k and 1M nodes; 310 and 1,150 where every node has
+  // one); the chunks are counted on the device.
+  //  - The level sweep with its preparation: 0.6 us a level and 5 ns a node after
+  //    0.55 ms, and where levels of fewer than 16k edges run in the ring 10 ns an
+  //    edge past 12 a node (32 edges a node: 90 ms at 200k nodes in 400 levels,
+  //    against 8.9 by 29 iterations).  Layered graphs of up to 1M nodes converge
+  //    after 17 to 38 iterations, the transformer graphs after 6 to 12: a budget
+  //    below 16 is left unused but for one (1M nodes, 24 edges a node, 33
+  //    iterations, b-level and t-level: 78 ms in full, 13 by the sweeps).
+  //  - Kahn's kernel: 10 ns a node after 0.1 ms, and some 2.5 ns an edge, taken
+  //    for the edges that the chunks stand for (2 ms at 200k nodes and 0.4M edges,
+  //    23 ms at 6.4M, 94 ms at 1M nodes and 24M); kLpKahnIt in any case.
+  // 16-byte entries: max_rounds barriers and passes over 48 bytes per node and
+  // one pass over the neighbour lists an iteration, against the sweep's levels.
+  LpArgs a{};
+  if (kind == 2) {
+    a.alt_us = 100.0f + 0.01f * (float)n;
+    a.alt_chunk_us = 2.5e-3f * 10.0f;
+    a.cap = a.few = a.less = kLpKahnIt;
+  } else {
+    a.alt_us = 550.0f + 0.6f * (float)L + 5e-3f * (float)n;
+    if ((int64_t)m < (int64_t)L * kLpWide && (int64_t)m > 12 * (int64_t)n)
+      a.alt_us += 0.01f * (float)((int64_t)m - 12 * (int64_t)n);
+    a.few = 16;
+    a.less = 1;
+    const double it_us = max_rounds * (5.0 + 48.0 * n / 4.0e6) + 12.0 * m / 4.0e6;
+    a.cap = (int32_t)((500.0 + 0.6 * L) / it_us);
+    if (a.cap < 2) a.cap = 2;
   }
   int32_t *hoff, *hnode, *pol, *hidx, *bar;
   LpE *e0, *e1;
@@ -519,9 +551,7 @@ int lp_policy(int32_t n, int32_t m, int32_t L, int32_t cap, const int32_t *aptr,
   k_lp_init<<<1, 256, 0, s>>>(bar, 3 + G, res);
   k_lp_lists<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, aptr, aidx, nb, hoff, hnode, bar + 2 + G, st);
   CEL_HIP(hipGetLastError());
-  LpArgs a{};
   a.n = n;
-  a.cap = cap;
   a.max_rounds = max_rounds;
   a.packed = policy_iteration_packed() ? 1 : 0;
   a.aptr = aptr;

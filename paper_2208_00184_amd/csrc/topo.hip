@@ -446,15 +446,6 @@ __global__ void __launch_bounds__(kKahnB) k_kahn(cel_graph g, int32_t *cnt, cons
 }
 
 constexpr int32_t kTopoPolicyN = 16384;  // smaller graphs take Kahn's kernel directly
-// Policy iterations before Kahn's kernel takes over: an iteration takes 37 us at
-// 200k nodes and 147 at 1.07M, Kahn's kernel 2.35 ms on the layered graph of
-// 200k nodes (which needs 19) and 17 ms on the transformer graph of 1.07M (8).
-constexpr int32_t kTopoPolicyIt = 12;
-inline int32_t topo_policy_cap(int32_t n) {
-  const double kahn_us = 100.0 + 0.01 * n, it_us = 25.0 + 1.2e-4 * n;
-  const int32_t c = (int32_t)(kahn_us / it_us);
-  return c > kTopoPolicyIt ? c : kTopoPolicyIt;
-}
 
 // wv = 1 for a node with predecessors, 0 for a source
 __global__ void k_topo_wv(int32_t n, const int32_t *in_ptr, int64_t *wv, const Status *st) {
@@ -541,8 +532,8 @@ extern "C" int cel_topo_levels(const cel_graph *g, int32_t *level, int32_t *orde
     k_topo_wv<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, g->in_ptr, wv, st);
     bool launched = false;
     GridTurn turn(s);
-    CEL_TRY(lp_policy(n, g->m, n, policy_iteration_packed() ? topo_policy_cap(n) : kTopoPolicyIt, g->in_ptr, g->in_idx, wv, 2, val, &st->i2,
-                      "k_levels_policy", sc, s, st, turn, &launched));
+    CEL_TRY(lp_policy(n, g->m, n, g->in_ptr, g->in_idx, wv, 2, val, &st->i2, "k_levels_policy", sc,
+                      s, st, turn, &launched));
     if (launched) {
       // order_id: the nodes sorted by (level, id), one segment, queued before
       // the status is read (one host round trip when the iteration

@@ -221,3 +221,34 @@ def test_policy_values_beyond_packed_entries():
     ref = O.cluster(wl, pr, 200, -1)
     cid, C, cut, (path, iters) = gpu_cluster(wl, pr, 200, -1)
     assert C == ref[1] and cut == ref[2] and np.array_equal(cid, ref[0])
+
+
+def wide_dag(n, width, deg, seed):
+    """Layers of `width` nodes, each node fed by `deg` of the eight layers before."""
+    rng = np.random.default_rng([n, width, deg, seed])
+    v = np.repeat(np.arange(width, n), deg)
+    u = np.maximum(v // width - rng.integers(1, 9, v.size), 0) * width + rng.integers(0, width, v.size)
+    return from_edges(n, np.stack([u, v], 1), rng.integers(1, 60, n), rng.integers(1, 400, n), 2, [10 ** 15] * 2, 7, 3)
+
+
+@pytest.mark.parametrize("deg,width,b_max", [(32, 1000, 2), (32, 100, 60), (4, 1000, 60)])
+def test_budget_follows_the_edges(deg, width, b_max, pi_mode):
+    """An iteration reads every edge: where all nodes have long lists and the
+    level sweep runs its wide levels on the whole GPU, one iteration is tried;
+    short lists, and levels that the sweep runs in its ring, iterate (packed
+    entries)."""
+    if pi_mode != 1:
+        return
+    wl = wide_dag(40000, width, deg, 1)
+    ref_t = O.topo_levels(wl)
+    ref_b = O.blevel(wl, ref_t[0], ref_t[1])
+    g, d = cel.Graph.from_arrays(wl, DEV), cel.Devices.from_arrays(wl)
+    lev, oid, lp, L = cel.topo_levels(g)
+    topo = cel.topo_levels_info()
+    bl, tl, prio, cp = cel.blevel(g, d, lev, lp, oid, L, want_tlevel=True)
+    info = cel.blevel_info()
+    print(f"[budget] deg {deg} width {width} levels {L} topo {topo} blevel {info}", flush=True)
+    assert L == ref_t[3] and np.array_equal(lev.cpu().numpy(), ref_t[0])
+    assert cp == ref_b[3] and np.array_equal(bl.cpu().numpy(), ref_b[0]) and np.array_equal(tl.cpu().numpy(), ref_b[1])
+    assert info[0][1] <= b_max and info[1][1] <= b_max
+    assert (info[0][0], info[1][0]) == ((1, 1) if b_max == 2 else (0, 0))
