@@ -190,13 +190,18 @@ constexpr int kBatchWide = 384;  // batches up to this size get one CU-sized win
 constexpr int kWideLevels = 256;  // mean level width from which batches skip the windows
 // Batches over narrow levels (mean width up to kBlocksWidth, kBlocksMin nodes
 // and more) run in blocks of tasks in LDS (ms_blocks.hip): their time follows
-// the nodes (some 7 ns each), the ring's the levels (0.45 to 0.85 us each).
-// Whole calls of 64 placements, ring -> blocks: inception-600 (width 8) 3,409 ->
-// 483 us, transformer-24 (width 10) 1,043 -> 362; layered graphs of width 37
-// 434 -> 443 (2 placements 427 -> 400, scattered ones 803 -> 491), of 46
-// (2,048 nodes) 177 -> 145; transformer-96 (width 101) 10,295 -> 10,943.
-// 1,670 nodes: 287 -> 136.
-constexpr int32_t kBlocksWidth = 48, kBlocksMin = 1024;
+// the nodes (some 7 ns each) and the placement with most iterations, the
+// ring's the levels (0.45 to 0.85 us each).  Whole calls of 64 placements, ring
+// -> blocks: inception-600 (width 8) 3,409 -> 483 us, transformer-24 (width 10)
+// 1,043 -> 362.  The more placements, the more iterations the slowest of them
+// takes, so that batches of more than kBlocksFew stop at a smaller width.
+// Layered graphs, clusterings with 5 % of the clusters moved (scattered nodes
+// in parentheses), width 34 to 40: 729 -> 581 us (1,549 -> 918), 662 -> 646
+// (1,366 -> 910) at 40,000 nodes and K = 64, 1,491 -> 1,373 at 100,000 and 256;
+// width 45: K = 8 594 -> 579, but K = 64 613 -> 623 and 1,229 -> 1,290, K = 256
+// 645 -> 739 (1,256 -> 958) and 1,352 -> 1,397.  Transformer-96 (width 101)
+// 10,295 -> 10,943.  1,670 nodes: 287 -> 136.
+constexpr int32_t kBlocksWidth = 48, kBlocksWidthMany = 40, kBlocksFew = 32, kBlocksMin = 1024;
 
 template <int B, int NC, int EC>
 __global__ void __launch_bounds__(B)
@@ -1005,8 +1010,8 @@ static int makespan_impl(const char *fn, const cel_graph *g, const cel_devices *
       // Narrow levels: the FIFO schedule in blocks of tasks in LDS; the ring
       // when values may reach 2^47 or the blocks need more iterations (1.2 us
       // and more each) than the ring takes.
-      if ((int64_t)n <= (int64_t)kBlocksWidth * L && n >= kBlocksMin &&
-          (int64_t)K * n <= kBkMaxTasks) {
+      const int32_t width = K <= kBlocksFew ? kBlocksWidth : kBlocksWidthMany;
+      if ((int64_t)n <= (int64_t)width * L && n >= kBlocksMin && (int64_t)K * n <= kBkMaxTasks) {
         const Scratch::Mark mk = sc.mark();
         int4 *ipre;
         CEL_TRY(sc.get(&ipre, n));

@@ -177,15 +177,17 @@ def test_batches_of_placements(n, D):
     assert n <= 48 * L  # narrow enough for the blocks (from 1,024 nodes on)
 
 
-@pytest.mark.parametrize("width", [47, 48, 49])
-def test_batches_by_level_width(width):
-    """Full levels of one width, each node fed by two of the level before."""
+@pytest.mark.parametrize("K,width,blocks", [(6, 47, True), (32, 48, True), (6, 49, False), (33, 40, True),
+                                            (33, 41, False)])
+def test_batches_by_level_width(K, width, blocks):
+    """Full levels of one width, each node fed by two of the level before;
+    batches of more than 32 leave the blocks at a smaller width."""
     n = 40 * width
     v = np.arange(width, n)
     rng = np.random.default_rng(width)
     e = np.concatenate([np.stack([(v // width - 1) * width + rng.integers(0, width, v.size), v], 1) for _ in range(2)])
     wl = from_edges(n, e, rng.integers(0, 60, n), rng.integers(0, 400, n), 8, [10 ** 15] * 8, 7, 3)
-    assert check_batch(wl, placements(n, 8, 6, 13), blocks=width <= 48) == 40
+    assert check_batch(wl, placements(n, 8, K, 13), blocks=blocks) == 40
 
 
 def test_batches_at_the_limits():
@@ -195,4 +197,4 @@ def test_batches_at_the_limits():
     check_batch(dag(9000, 6, 15, fan=40, reach=90, hubs=((4000, 3000), (8191, 17000))), placements(9000, 6, 4, 15))
     n, rng = 3000, np.random.default_rng(16)
     L = check_batch(dag(n, 3, 16, reach=20, ob_max=4000, w_max=3), rng.integers(0, 3, (300, n)).astype(np.uint8))
-    assert n <= 48 * L
+    assert n <= 40 * L
