@@ -28,7 +28,7 @@
 //     clusters leave few nodes to gaps: 16 placements of 55,003 nodes on 8
 //     devices, 877 segments a placement and no miss, where every edge ended a
 //     segment and every slot was placed by itself 7,775 and 54,387; 17.9 ->
-//     2.5 ms.  Devices at random, node by node: 2 to 4 % slower.)
+//     2.5 ms.  Devices at random, node by node, take a walk without guesses.)
 //     Device d's state (free time or end of its last task, gap count and
 //     ring head, channel free times) lives in lane d.  The segment's
 //     transfers are then issued in slot order.
@@ -82,6 +82,7 @@ struct MmArgs {
   const int64_t *tmul;         // [D] time multipliers, 1/1024 (HET)
   const int64_t *lbw, *llat;   // [D][D] links (HET)
   const int4 *ipre;            // first 4 inputs of each position (-1 past the row's end)
+  const int32_t *same;        // insertion: positions on the device of the one before, per placement
 };
 
 constexpr int kHetD = 64;  // link table stride
@@ -431,30 +432,14 @@ __device__ inline bool lane_insert(int64_t *A, int64_t *B, int64_t *ta, int64_t 
   return true;
 }
 
-template <bool INS, bool TASKS, bool HET, bool BLOCK = false>
-__global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
-  // transfers whose arrivals the inputs read: on channels (TASKS) or on the
-  // devices' compute queues (BLOCK)
+// A placement's walk (the state of k_makespan_model's workgroup in LDS).
+// GUESS: with insertion, windows may be guessed.
+template <bool INS, bool TASKS, bool HET, bool BLOCK, bool GUESS>
+__device__ __forceinline__ void mm_walk(const MmArgs &a, Status *st, int64_t tmr, int64_t *s_T,
+                                        const int32_t *s_bw, const int32_t *s_lat, int64_t *s_ta,
+                                        int64_t *s_tb, unsigned long long *s_lst, int64_t *s_fin) {
   constexpr bool ARR = TASKS || BLOCK;
-  static_assert(!(BLOCK && (INS || TASKS)), "the blocking model combines with no other bit");
-  __shared__ int64_t s_T[ARR ? 64 * 64 : 1];  // arrival of slot j's output on device b
-  __shared__ int32_t s_bw[HET ? kHetD * kHetD : 1], s_lat[HET ? kHetD * kHetD : 1];
-  __shared__ int64_t s_ta[INS ? 64 * kTail : 1], s_tb[INS ? 64 * kTail : 1];  // gap tails
-  __shared__ unsigned long long s_lst[64];  // slots of the segment by device
-  __shared__ int64_t s_fin[64];             // finish of the segment's slots
-  if (failed(st)) return;
   const int lane = threadIdx.x;
-  s_lst[lane] = 0;
-  int64_t tmr = 1024;  // device `lane`'s time multiplier
-  if (HET) {
-    for (int i = lane; i < a.D * a.D; i += 64) {
-      const int x = i / a.D, y = i - x * a.D;
-      s_bw[x * kHetD + y] = (int32_t)a.lbw[i];
-      s_lat[x * kHetD + y] = (int32_t)a.llat[i];
-    }
-    if (lane < a.D) tmr = a.tmul[lane];
-    __syncthreads();
-  }
   const int64_t k = blockIdx.x;
   const int32_t n = a.n;
   const uint8_t *dev = a.devp + k * n;
@@ -468,7 +453,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
   int64_t gbase = INS && lane < a.D ? a.goff[k * a.D + lane] : 0;
   int32_t ghead = 0;  // ring head of the gap tail
   int64_t snd = 0, rcv = 0, tcur = 0;
-  int32_t careful = 0, hold = 1;  // windows to place one slot at a time (insertion)
+  int32_t careful = 0, hold = 1;  // windows to place one slot at a time (GUESS)
   int64_t span = 0;
   uint32_t bad = 0;
   // A slot's own values and its first 4 inputs depend on nothing computed
@@ -553,7 +538,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
     // insertion a slot without duration is outside that order.
     uint64_t cmsk = msk;
     bool guess = false;  // enough slots on one device to place them all at once
-    if (!BLOCK && careful == 0) {
+    if (INS ? GUESS && careful == 0 : !BLOCK) {
       uint64_t own = __ballot(act);
       for (int b = 0; b < 6; b++) {
         const uint64_t x = __ballot((dv >> b) & 1);
@@ -568,7 +553,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
     int miss = 0;        // segments of this window that held a slot for a gap
     bool skip = false;   // the next segment starts with one
     for (int32_t s0 = 0; s0 < nw;) {
-      const bool spec = INS && guess && miss < kInsMiss && !skip;
+      const bool spec = GUESS && guess && miss < kInsMiss && !skip;
       skip = false;
       const uint64_t cm = INS && !spec ? msk : cmsk;
       const uint64_t cut = __ballot(lane > s0 && lane < nw && (cm & ~below(s0)) != 0);
@@ -625,7 +610,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
         continue;
       }
       bool placed = false;
-      while (INS && spec && !placed) {
+      while (GUESS && spec && !placed) {
         // Every slot after its device's last task, as FIFO devices have it:
         // right for all slots that no idle gap ends after.
         const int32_t d0 = __builtin_amdgcn_readlane(dv, s0);
@@ -731,7 +716,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
           if (end > first) last = nl;
         }
       }
-      if (INS && spec && !placed) {  // by gaps, up to the next edge of any kind
+      if (GUESS && spec && !placed) {  // by gaps, up to the next edge of any kind
         const uint64_t c2 = __ballot(lane > s0 && lane < nw && (msk & ~below(s0)) != 0);
         s1 = c2 ? __builtin_ctzll(c2) : nw;
         inseg = lane >= s0 && lane < s1;
@@ -855,7 +840,7 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
       }
       s0 = s1;
     }
-    if (INS) {  // many slots in gaps: the next windows one slot at a time
+    if (GUESS) {  // many slots in gaps: the next windows one slot at a time
       if (careful > 0) {
         careful--;
       } else if (miss >= kInsMiss) {
@@ -884,6 +869,49 @@ __global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
   if (bad) raise_err(st, bad);
 }
 
+// Insertion: which placements guess their windows.  Those whose neighbours in
+// order mostly share a device do (clusterings: 96 % of the windows and more have
+// 40 slots on one device), scattered ones do not; each has a walk of its own,
+// since the guess's registers and tests in the plain one cost it up to 9 % (16
+// scattered placements of inception-600 15.1 -> 16.4 ms, apart 14.9).  Both walks
+// in one kernel cost clusterings with transfer tasks 2 to 3 %, so where the host
+// has read the counts anyway it picks the kernel.
+enum MmGuess { kMmPlain = 0, kMmGuess = 1, kMmEach = 2 };
+
+__host__ __device__ inline bool mm_guesses(int32_t n, int32_t same) {
+  return 4 * (int64_t)same >= 3 * ((int64_t)n - 1);
+}
+
+template <bool INS, bool TASKS, bool HET, bool BLOCK = false, int MODE = INS ? kMmEach : kMmPlain>
+__global__ void __launch_bounds__(64) k_makespan_model(MmArgs a, Status *st) {
+  // transfers whose arrivals the inputs read: on channels (TASKS) or on the
+  // devices' compute queues (BLOCK)
+  constexpr bool ARR = TASKS || BLOCK;
+  static_assert(!(BLOCK && (INS || TASKS)), "the blocking model combines with no other bit");
+  __shared__ int64_t s_T[ARR ? 64 * 64 : 1];  // arrival of slot j's output on device b
+  __shared__ int32_t s_bw[HET ? kHetD * kHetD : 1], s_lat[HET ? kHetD * kHetD : 1];
+  __shared__ int64_t s_ta[INS ? 64 * kTail : 1], s_tb[INS ? 64 * kTail : 1];  // gap tails
+  __shared__ unsigned long long s_lst[64];  // slots of the segment by device
+  __shared__ int64_t s_fin[64];             // finish of the segment's slots
+  if (failed(st)) return;
+  const int lane = threadIdx.x;
+  s_lst[lane] = 0;
+  int64_t tmr = 1024;  // device `lane`'s time multiplier
+  if (HET) {
+    for (int i = lane; i < a.D * a.D; i += 64) {
+      const int x = i / a.D, y = i - x * a.D;
+      s_bw[x * kHetD + y] = (int32_t)a.lbw[i];
+      s_lat[x * kHetD + y] = (int32_t)a.llat[i];
+    }
+    if (lane < a.D) tmr = a.tmul[lane];
+    __syncthreads();
+  }
+  if (MODE == kMmGuess || (MODE == kMmEach && mm_guesses(a.n, a.same[blockIdx.x])))
+    mm_walk<INS, TASKS, HET, BLOCK, MODE != kMmPlain>(a, st, tmr, s_T, s_bw, s_lat, s_ta, s_tb, s_lst, s_fin);
+  else
+    mm_walk<INS, TASKS, HET, BLOCK, false>(a, st, tmr, s_T, s_bw, s_lat, s_ta, s_tb, s_lst, s_fin);
+}
+
 // First 4 inputs of each position (position space, -1 past the row's end),
 // so that a window's inputs load with its other per-slot values.
 __global__ void k_mm_ipre(int32_t n, const int32_t *iptr, const int32_t *iidx, int4 *ipre,
@@ -897,20 +925,26 @@ __global__ void k_mm_ipre(int32_t n, const int32_t *iptr, const int32_t *iidx, i
   }
 }
 
-// Per placement, nodes per device (gap segment sizes); blocks take chunks of
-// positions and add an LDS histogram into cnt[k][D].
+// Per placement, nodes per device (gap segment sizes) and positions on the
+// device of the one before; blocks take chunks of positions and add an LDS
+// histogram into cnt[k][D] and same[k].
 __global__ void k_mm_devcount(int32_t K, int32_t n, int32_t D, const uint8_t *devp, int32_t *cnt,
-                              const Status *st) {
-  __shared__ int32_t h[64];
+                              int32_t *same, const Status *st) {
+  __shared__ int32_t h[65];
   if (failed(st)) return;
   for (int64_t k = blockIdx.y; k < K; k += gridDim.y) {
-    if (threadIdx.x < 64) h[threadIdx.x] = 0;
+    if (threadIdx.x < 65) h[threadIdx.x] = 0;
     __syncthreads();
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-         p += (int64_t)gridDim.x * blockDim.x)
-      atomicAdd(&h[devp[k * n + p]], 1);
+         p += (int64_t)gridDim.x * blockDim.x) {
+      const int32_t d = devp[k * n + p];
+      atomicAdd(&h[d], 1);
+      const uint64_t s = __ballot(p > 0 && devp[k * n + p - 1] == d);
+      if ((int)(threadIdx.x & 63) == __builtin_ctzll(s | 1ull << 63)) atomicAdd(&h[64], __popcll(s));
+    }
     __syncthreads();
     if (threadIdx.x < D && h[threadIdx.x]) atomicAdd(&cnt[k * D + threadIdx.x], h[threadIdx.x]);
+    if (threadIdx.x == 0 && h[64]) atomicAdd(&same[k], h[64]);
     __syncthreads();
   }
 }
@@ -1144,18 +1178,21 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
   if (ins) {
     int32_t *cnt;
     int64_t *goff, *ga, *gb;
-    CEL_TRY(sc.get(&cnt, (int64_t)K * D));
+    CEL_TRY(sc.get(&cnt, (int64_t)K * (D + 1)));  // and same[K]
     CEL_TRY(sc.get(&goff, (int64_t)K * D));
     CEL_TRY(sc.get(&ga, Kn));
     CEL_TRY(sc.get(&gb, Kn));
-    CEL_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * K * D, s));
-    k_mm_devcount<<<dim3(grid_for(n, 256, 64), gy), 256, 0, s>>>(K, n, D, devp, cnt, st);
+    int32_t *same = cnt + (int64_t)K * D;
+    CEL_HIP(hipMemsetAsync(cnt, 0, sizeof(int32_t) * K * (D + 1), s));
+    k_mm_devcount<<<dim3(grid_for(n, 256, 64), gy), 256, 0, s>>>(K, n, D, devp, cnt, same, st);
+    a.same = same;
     k_mm_goff<<<grid_for(K, 256, 1024), 256, 0, s>>>(K, n, D, cnt, goff, st);
     a.goff = goff;
     a.ga = ga;
     a.gb = gb;
   }
   int64_t total = 0;  // transfers of all placements (valid once the checks passed)
+  int32_t guessing = -1;  // placements that guess their windows, once known
   if (tasks || block) {
     uint64_t *dmask;
     int64_t *pc, *aoff;
@@ -1168,9 +1205,16 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
     k_mm_popc<<<grid_for(Kn, 256, 8192), 256, 0, s>>>(Kn, dmask, pc, st);
     CEL_TRY(exclusive_scan_i64(pc, aoff, Kn, sc, s));
     CEL_HIP(hipMemcpyAsync(&total, aoff + Kn, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    std::vector<int32_t> same(ins ? K : 0);
+    if (ins)
+      CEL_HIP(hipMemcpyAsync(same.data(), a.same, sizeof(int32_t) * K, hipMemcpyDeviceToHost, s));
     Status h0;
     CEL_TRY(read_status(st, &h0, s));
     if (h0.err) return status_error(h0, fn);
+    if (ins) {
+      guessing = 0;
+      for (const int32_t x : same) guessing += mm_guesses(n, x) ? 1 : 0;
+    }
     a.dmask = dmask;
     a.aoff = aoff;
   }
@@ -1228,11 +1272,15 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
       if (!ins && !tasks) k_makespan_model<false, false, true><<<gk, 64, 0, s>>>(a, st);
       else if (ins && !tasks) k_makespan_model<true, false, true><<<gk, 64, 0, s>>>(a, st);
       else if (!ins) k_makespan_model<false, true, true><<<gk, 64, 0, s>>>(a, st);
+      else if (guessing == K) k_makespan_model<true, true, true, false, kMmGuess><<<gk, 64, 0, s>>>(a, st);
+      else if (guessing == 0) k_makespan_model<true, true, true, false, kMmPlain><<<gk, 64, 0, s>>>(a, st);
       else k_makespan_model<true, true, true><<<gk, 64, 0, s>>>(a, st);
     } else {
       if (!ins && !tasks) k_makespan_model<false, false, false><<<gk, 64, 0, s>>>(a, st);
       else if (ins && !tasks) k_makespan_model<true, false, false><<<gk, 64, 0, s>>>(a, st);
       else if (!ins) k_makespan_model<false, true, false><<<gk, 64, 0, s>>>(a, st);
+      else if (guessing == K) k_makespan_model<true, true, false, false, kMmGuess><<<gk, 64, 0, s>>>(a, st);
+      else if (guessing == 0) k_makespan_model<true, true, false, false, kMmPlain><<<gk, 64, 0, s>>>(a, st);
       else k_makespan_model<true, true, false><<<gk, 64, 0, s>>>(a, st);
     }
   }

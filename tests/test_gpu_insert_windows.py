@@ -103,3 +103,18 @@ def test_full_windows(model):
     for D in (1, 2, 5, 64):
         wl = from_edges(n, e, rng.integers(0, 30, n), rng.integers(0, 600, n), D, [10 ** 15] * D, 7, 3)
         check(wl, placements(n, D, 11), model)
+
+
+@pytest.mark.parametrize("model", MODELS)
+@pytest.mark.parametrize("runs", [(1,), (1, 2, 3), (2, 3, 4, 5), (8, 64), (1, 64, 1000)])
+def test_scattered_and_clustered_batches(model, runs):
+    """Batches of scattered placements only, of clusterings only and of both:
+    a placement guesses its windows from three of four neighbours on one
+    device on."""
+    n, D = 5000, 8
+    rng = np.random.default_rng(12)
+    wl = dag(n, D, 13, 60, (1, 60), (0, 400), 0.1, 0.05)
+    P = np.stack([np.repeat(rng.integers(0, D, n // r + 1), r)[:n] for r in runs])
+    check(wl, P, model)
+    check(wl, P, model, tmul=[int(x) for x in rng.integers(512, 2048, D)], bw=rng.integers(1, 40, (D, D)).tolist(),
+          lat=rng.integers(0, 50, (D, D)).tolist())
