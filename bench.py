@@ -78,8 +78,10 @@ PMC_KERNELS = {
     "k_makespan_batch_wide": ("cel::(anonymous namespace)::k_mw_batch(", ["ms_wide.hip", "cel_internal.h"]),
     "k_kahn": ("cel::k_kahn(", ["topo.hip", "cel_internal.h"]),
     "k_cluster_dp": ("cel::k_cluster_dp<true>(", ["cluster.hip", "cel_internal.h"]),
-    "k_cluster_policy": ("cel::k_dp_policy(", ["dp_policy.hip", "cel_internal.h"]),
-    "k_place": ("cel::k_place<", ["place.hip", "cel_internal.h"]),
+    "k_cluster_policy": ("cel::k_dp_tiles<", ["dp_policy.hip", "cel_internal.h"]),
+    "k_place": ("cel::k_place_ahead<false", ["place.hip", "cel_internal.h"]),
+    "k_place_ext": ("cel::k_place_ahead<true", ["place.hip", "cel_internal.h"]),
+    "k_makespan_model": ("cel::k_ms_blocks<", ["ms_blocks.hip", "cel_internal.h"]),
 }
 
 

@@ -278,7 +278,7 @@ constexpr int kPlacePad = 64 * kPlaceQ;           // entries read past the end o
 // a list that outgrows its share, or a longer pred list, stops the kernel
 // with st->i1 = 1, and the caller runs the GL = true kernel, whose lists move
 // to global memory when full and whose long pred lists are read in passes.
-template <bool LDSF, bool GL, int NI>  // NI: devices per lane (D <= 64 NI)
+template <bool LDSF, bool GL>
 __global__ void __launch_bounds__(64)
     k_place(int32_t C, int32_t D, const int64_t *cap, const uint64_t *W, const uint64_t *MEM,
             const int32_t *boff, const int32_t *ncp, const int32_t *ca, const int64_t *cc,
@@ -288,6 +288,7 @@ __global__ void __launch_bounds__(64)
   __shared__ int64_t s_fin[LDSF ? kPlaceLds : 1];
   __shared__ uint8_t s_cd[LDSF ? kPlaceLds : 1];
   if (failed(st)) return;
+  constexpr int NI = 4;  // devices per lane (D <= 255)
   const int lane = threadIdx.x;
   const int32_t capL = kPlaceBlk / D;
   int64_t ava[NI], last[NI];  // device lane + 64 i: free memory, end of its last busy block
@@ -453,7 +454,7 @@ __global__ void __launch_bounds__(64)
     int64_t e = kPlaceFull - est[0];
 #pragma unroll
     for (int i = 1; i < NI; i++) e = max_nonneg(e, kPlaceFull - est[i]);
-    const int64_t ev = kPlaceFull - (D <= 16 ? wave_max_nonneg<false>(e) : wave_max_nonneg<true>(e));
+    const int64_t ev = kPlaceFull - wave_max_nonneg<true>(e);
     int32_t ei = 0;
     if (ev < kPlaceFull) {
 #pragma unroll
@@ -1327,7 +1328,7 @@ extern "C" int cel_place(const cel_graph *g, const cel_devices *d, const int32_t
     {
       KTimer kt(s, "k_place");
 #define CEL_PLACE_LAUNCH(LDSF, GL)                                                              \
-  k_place<LDSF, GL, 4><<<1, 64, 0, s>>>(C, d->D, dcap, W, MEM, boff, ncp, ca, cc, back,         \
+  k_place<LDSF, GL><<<1, 64, 0, s>>>(C, d->D, dcap, W, MEM, boff, ncp, ca, cc, back,         \
                                         cluster_dev, Fin, bs, bf, (int32_t)bcap, st)
       const bool lds = C <= kPlaceLds;
       if (lds && !gl) CEL_PLACE_LAUNCH(true, false);
