@@ -259,7 +259,7 @@ __device__ inline void lds_st(uint64_t *p, uint64_t v) {
 
 // XFER: tasks with transfers; otherwise nodes alone, a cross-device input
 // costing c (HET: its link's cost) on the edge.  (<false, true> spills 96 bytes a
-// lane, outside the jumps: the link costs' divisions at 1,024 threads.)
+// lane, outside the iterations: 1,024 threads leave a lane 128 registers.)
 template <bool XFER, bool HET>
 __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
   constexpr int kKeys = XFER ? 192 : (HET ? 64 : 256);
