@@ -273,6 +273,7 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
   __shared__ int32_t s_bw[HET ? 64 * 64 : 1], s_lat[HET ? 64 * 64 : 1];
   __shared__ int64_t s_red[kBkT / 64];
   __shared__ int32_t s_ovn, s_f, s_chg[3];
+  __shared__ int32_t s_blk;  // blocks that ended (thread 0; a register more costs 2 %)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) {
     s_f = failed(st) ? 1 : 0;
@@ -296,7 +297,7 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
   const uint8_t *dev = a.devp + kn;
   int64_t *val = a.val + t0;
   int64_t span = 0;
-  int32_t its = 0, nblk = 0, nt = 0;  // nblk: blocks that ended
+  int32_t its = 0, nt = 0;
   int32_t pp0 = 0;  // the previous block's first task
   if (tid == 0) {
     s_ent[0][kBkB] = s_ent[1][kBkB] = kEnd;
@@ -305,6 +306,7 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
       s_dev[kBkB] = 0;
     }
     s_chg[0] = s_chg[1] = s_chg[2] = 0;
+    s_blk = 0;
   }
   struct Task {  // a task's own data, read a block ahead
     int64_t wv, c;
@@ -569,15 +571,18 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
       if (__ballot(chg) && lane == 0) s_chg[i] = 1;
       if (tid == 0) s_chg[i == 2 ? 0 : i + 1] = 0;  // last read two iterations ago
       lds_barrier();
-      if (!s_chg[i]) break;
-      if (its > a.budget) {  // uniform: the caller runs the other method
+      const bool more = s_chg[i] != 0;
+      // uniform, and whether or not this block needs more: the caller runs the
+      // other method
+      if (its > a.budget && (more || p0 + nt < N)) {
         if (tid == 0) {
           atomicOr(&st->i1, 1);
           atomicMax(&st->i2, its);
-          atomicMax(&st->i3, nblk);
+          atomicMax(&st->i3, s_blk);
         }
         return;
       }
+      if (!more) break;
     }
     // ---- the block's finish times
 #pragma unroll
@@ -589,21 +594,13 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
       if (inf[u] & kBkLast1) s_free[kk[u] & 255u] = v[u];
       if (XFER && (inf[u] & kBkLast2)) s_free[kk[u] >> 8] = v[u];
     }
-    nblk++;
+    if (tid == 0) atomicAdd(&s_blk, 1);  // (no wait)
     pp0 = p0;
     p0 += nt;
     par ^= 1;
     lim = 2 * lim < kBkB ? 2 * lim : kBkB;
     lds_barrier();
     if (tid == 0) s_chg[0] = 0;  // the next block's first flag, read behind two more barriers
-    if (its > a.budget && p0 < N) {  // as above, whatever the block needed
-      if (tid == 0) {
-        atomicOr(&st->i1, 1);
-        atomicMax(&st->i2, its);
-        atomicMax(&st->i3, nblk);
-      }
-      return;
-    }
   }
   for (int o = 32; o > 0; o >>= 1) span = max_nonneg(span, (int64_t)__shfl_xor((long long)span, o));
   if (lane == 0) s_red[wave] = span;
@@ -612,7 +609,7 @@ __global__ void __launch_bounds__(kBkT) k_ms_blocks(BkArgs a, Status *st) {
     for (int i = 1; i < kBkT / 64; i++) span = max_nonneg(span, s_red[i]);
     a.makespan[blockIdx.x] = span;
     atomicMax(&st->i2, its);
-    atomicMax(&st->i3, nblk);
+    atomicMax(&st->i3, s_blk);
   }
 }
 
