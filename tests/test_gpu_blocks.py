@@ -116,6 +116,20 @@ def test_listed_inputs_do_not_fit():
         assert blocks <= 24  # 3 chunks of nodes alone, 5 with transfers
 
 
+def test_budget_spent_on_small_blocks():
+    """Forty nodes of 20,000 parallel in-edges each: small blocks one after the
+    other spend the budget of iterations (64 + 0.035 n), and the call stops
+    there and walks."""
+    wl = dag(4500, 3, 18)
+    rng = np.random.default_rng(19)
+    hub = 200 + 100 * np.arange(40)
+    src = np.concatenate([np.repeat(np.arange(wl.n), np.diff(wl.out_ptr))] + [rng.integers(h - 90, h, 20000) for h in hub])
+    dst = np.concatenate([wl.out_idx, np.repeat(hub, 20000)])
+    wl = from_edges(wl.n, np.stack([src, dst], 1), wl.w, wl.ob, 3, [10 ** 15] * 3, 7, 3)
+    its, blocks = check_model(wl, placements(4500, 3, 2, 18), 0, blocks=False)
+    assert 221 < its <= 260 and blocks > 20
+
+
 def test_rows_longer_than_the_list():
     """Nodes fed by every node before them, 17,000 to 19,999 inputs, two in one
     block: only the inputs beside them are listed, so no block is halved."""
