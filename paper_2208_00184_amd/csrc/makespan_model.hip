@@ -874,8 +874,11 @@ __device__ __forceinline__ void mm_walk(const MmArgs &a, Status *st, int64_t tmr
 // 40 slots on one device), scattered ones do not; each has a walk of its own,
 // since the guess's registers and tests in the plain one cost it up to 9 % (16
 // scattered placements of inception-600 15.1 -> 16.4 ms, apart 14.9).  Both walks
-// in one kernel cost clusterings with transfer tasks 2 to 3 %, so where the host
-// has read the counts anyway it picks the kernel.
+// in one kernel cost clusterings with transfer tasks 2 to 3 % and gap-heavy ones
+// on mixed devices 4 % (1.07M nodes 259 -> 270 ms), so where the host reads the
+// counts it picks the kernel: with transfers, whose number it reads anyway, and
+// from kMmPickN nodes on, where a walk takes 6 ms and more.
+constexpr int32_t kMmPickN = 1 << 17;
 enum MmGuess { kMmPlain = 0, kMmGuess = 1, kMmEach = 2 };
 
 __host__ __device__ inline bool mm_guesses(int32_t n, int32_t same) {
@@ -1193,6 +1196,18 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
   }
   int64_t total = 0;  // transfers of all placements (valid once the checks passed)
   int32_t guessing = -1;  // placements that guess their windows, once known
+  // the status, and with insertion the counts
+  auto read_counts = [&]() -> int {
+    std::vector<int32_t> same(ins ? K : 0);
+    if (ins)
+      CEL_HIP(hipMemcpyAsync(same.data(), a.same, sizeof(int32_t) * K, hipMemcpyDeviceToHost, s));
+    Status h0;
+    CEL_TRY(read_status(st, &h0, s));
+    if (h0.err) return status_error(h0, fn);
+    if (ins) guessing = 0;
+    for (const int32_t x : same) guessing += mm_guesses(n, x) ? 1 : 0;
+    return CEL_OK;
+  };
   if (tasks || block) {
     uint64_t *dmask;
     int64_t *pc, *aoff;
@@ -1205,19 +1220,11 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
     k_mm_popc<<<grid_for(Kn, 256, 8192), 256, 0, s>>>(Kn, dmask, pc, st);
     CEL_TRY(exclusive_scan_i64(pc, aoff, Kn, sc, s));
     CEL_HIP(hipMemcpyAsync(&total, aoff + Kn, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    std::vector<int32_t> same(ins ? K : 0);
-    if (ins)
-      CEL_HIP(hipMemcpyAsync(same.data(), a.same, sizeof(int32_t) * K, hipMemcpyDeviceToHost, s));
-    Status h0;
-    CEL_TRY(read_status(st, &h0, s));
-    if (h0.err) return status_error(h0, fn);
-    if (ins) {
-      guessing = 0;
-      for (const int32_t x : same) guessing += mm_guesses(n, x) ? 1 : 0;
-    }
+    CEL_TRY(read_counts());
     a.dmask = dmask;
     a.aoff = aoff;
   }
+  if (ins && !tasks && n >= kMmPickN) CEL_TRY(read_counts());
   // Without insertion every start is fixed by the order: blocks of tasks in
   // LDS.  The walk below when values may need more than 47 bits, when the
   // blocks need more iterations (about 1.2 us each) than the walk takes (42 ns
@@ -1265,24 +1272,30 @@ extern "C" int cel_makespan_model(const cel_graph *g, const cel_devices *d, cons
   {
     KTimer kt(s, "k_makespan_model");
     const unsigned gk = (unsigned)K;
+#define CEL_MM_INS(T, H)                                                               \
+  do {                                                                                 \
+    if (guessing == K)                                                                 \
+      k_makespan_model<true, T, H, false, kMmGuess><<<gk, 64, 0, s>>>(a, st);          \
+    else if (guessing == 0)                                                            \
+      k_makespan_model<true, T, H, false, kMmPlain><<<gk, 64, 0, s>>>(a, st);          \
+    else                                                                               \
+      k_makespan_model<true, T, H><<<gk, 64, 0, s>>>(a, st);                           \
+  } while (0)
     if (block) {
       if (het) k_makespan_model<false, false, true, true><<<gk, 64, 0, s>>>(a, st);
       else k_makespan_model<false, false, false, true><<<gk, 64, 0, s>>>(a, st);
     } else if (het) {
       if (!ins && !tasks) k_makespan_model<false, false, true><<<gk, 64, 0, s>>>(a, st);
-      else if (ins && !tasks) k_makespan_model<true, false, true><<<gk, 64, 0, s>>>(a, st);
+      else if (ins && !tasks) CEL_MM_INS(false, true);
       else if (!ins) k_makespan_model<false, true, true><<<gk, 64, 0, s>>>(a, st);
-      else if (guessing == K) k_makespan_model<true, true, true, false, kMmGuess><<<gk, 64, 0, s>>>(a, st);
-      else if (guessing == 0) k_makespan_model<true, true, true, false, kMmPlain><<<gk, 64, 0, s>>>(a, st);
-      else k_makespan_model<true, true, true><<<gk, 64, 0, s>>>(a, st);
+      else CEL_MM_INS(true, true);
     } else {
       if (!ins && !tasks) k_makespan_model<false, false, false><<<gk, 64, 0, s>>>(a, st);
-      else if (ins && !tasks) k_makespan_model<true, false, false><<<gk, 64, 0, s>>>(a, st);
+      else if (ins && !tasks) CEL_MM_INS(false, false);
       else if (!ins) k_makespan_model<false, true, false><<<gk, 64, 0, s>>>(a, st);
-      else if (guessing == K) k_makespan_model<true, true, false, false, kMmGuess><<<gk, 64, 0, s>>>(a, st);
-      else if (guessing == 0) k_makespan_model<true, true, false, false, kMmPlain><<<gk, 64, 0, s>>>(a, st);
-      else k_makespan_model<true, true, false><<<gk, 64, 0, s>>>(a, st);
+      else CEL_MM_INS(true, false);
     }
+#undef CEL_MM_INS
   }
   if (start || finish)
     k_mm_out<<<grid_for(Kn, 256, 8192), 256, 0, s>>>(K, n, order, finp, wp, devp, tmul_d, start,

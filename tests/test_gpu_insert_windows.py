@@ -118,3 +118,13 @@ def test_scattered_and_clustered_batches(model, runs):
     check(wl, P, model)
     check(wl, P, model, tmul=[int(x) for x in rng.integers(512, 2048, D)], bw=rng.integers(1, 40, (D, D)).tolist(),
           lat=rng.integers(0, 50, (D, D)).tolist())
+
+
+@pytest.mark.parametrize("runs", [(1,), (64,), (1, 64)])
+def test_large_graphs_pick_their_walk(runs):
+    """From 131,072 nodes on the host picks the walk without transfers too."""
+    n, D = 131072, 4
+    rng = np.random.default_rng(14)
+    wl = dag(n, D, 15, 200, (1, 60), (0, 400), 0.0, 0.02)
+    P = np.stack([np.repeat(rng.integers(0, D, n // r + 1), r)[:n] for r in runs])
+    check(wl, P, cel.MODEL_INSERT)
