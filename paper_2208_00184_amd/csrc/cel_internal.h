@@ -371,6 +371,7 @@ class GridTurn {
  private:
   hipStream_t s_;
   std::timed_mutex *mu_ = nullptr;
+  bool late_ = false;
 };
 
 // Launch-configuration helpers

@@ -181,7 +181,10 @@ bool GridTurn::take() {
     if (!t) t = new std::timed_mutex();
     m = t;
   }
-  if (!m->try_lock_for(kTurnWait)) return false;
+  if (late_ ? !m->try_lock() : !m->try_lock_for(kTurnWait)) {
+    late_ = true;  // a call waits once
+    return false;
+  }
   mu_ = m;
   return true;
 }

@@ -4,6 +4,7 @@ take turns, and every call gives the oracle's results."""
 from __future__ import annotations
 
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -72,3 +73,47 @@ def test_plans_on_four_streams():
     for t in ts:
         t.join()
     assert not errors, errors
+
+
+def test_call_without_a_turn():
+    """A call whose stream is behind a caller's long kernel holds the turn; one
+    on another stream waits a second for it, then takes the blocked DP."""
+    wl = near_dag(16384, 4)
+    ref = O.cluster(wl, np.arange(wl.n), 64, -1)
+    g, d = cel.Graph.from_arrays(wl, DEV), cel.Devices.from_arrays(wl)
+    order = torch.arange(wl.n, dtype=torch.int32, device=DEV)
+    cel.cluster(g, d, order, 64, -1)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    ev[0].record()
+    torch.cuda._sleep(1 << 24)
+    ev[1].record()
+    torch.cuda.synchronize()
+    cycles = int((1 << 24) * 2500.0 / max(ev[0].elapsed_time(ev[1]), 1e-3))  # 2.5 s
+    errors, queued = [], threading.Event()
+
+    def holder():
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                torch.cuda._sleep(cycles)
+                queued.set()
+                lev, _, _, L = cel.topo_levels(g)  # takes the turn, then waits for the kernel before it
+                assert L == O.topo_levels(wl)[3] and cel.topo_levels_info()[0] == 0
+        except BaseException as e:  # noqa: BLE001 (reported by the test's thread)
+            errors.append(repr(e))
+
+    t = threading.Thread(target=holder)
+    t.start()
+    queued.wait()
+    time.sleep(0.3)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        t0 = time.perf_counter()
+        cid, C, cut = cel.cluster(g, d, order, 64, -1)
+        waited = time.perf_counter() - t0
+    info = cel.cluster_info()
+    t.join()
+    print(f"[turn] waited {waited:.2f} s, {info}", flush=True)
+    assert not errors, errors
+    assert (C, cut) == (ref[1], ref[2]) and np.array_equal(cid.cpu().numpy(), ref[0])
+    assert info == (1, 0) and 0.9 < waited < 1.3
